@@ -9,6 +9,7 @@
 namespace tdes {
 
 hipError_t launch_auto(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, hipStream_t stream) {
+    if (n_blocks < kShortBelow) return launch_short_ecb(ks, in, out, n_blocks, stream);
     return n_blocks < kAutoTableBelow ? launch_table(ks, in, out, n_blocks, stream)
                                       : launch_bitslice(ks, in, out, n_blocks, stream);
 }
@@ -55,16 +56,20 @@ int check_buffers(const void *dev_sched, const void *in, const void *out, uint64
     return TDES_OK;
 }
 
-// The automatic choice, on MI355X measurements of one launch (encrypt, HIP
-// events around the launch): the bitsliced kernel costs about 36 us for
+// One launch of a variant.  The automatic choice (internal.h), on MI355X measurements of one launch
+// (encrypt, HIP events around the launch): the bitsliced kernel costs about 36 us for
 // anything up to 2^18 blocks (one wave runs a whole 2048-block tile through all
 // 48 rounds) and then scales at about 900 GB/s; the table kernel costs 8-13 us
 // up to 2^16 blocks (14 us at 2^18; the spread is the launch cost of different
 // machines) and scales at about 260 GB/s.  At 2^20 blocks the bitsliced kernel
-// is already ahead (39 vs 42 us).
-int resolve_variant(int variant, uint64_t n_blocks) {
-    if (variant == TDES_VARIANT_AUTO) return n_blocks < tdes::kAutoTableBelow ? TDES_VARIANT_TABLE : TDES_VARIANT_BITSLICE;
-    return variant;
+// is already ahead (39 vs 42 us).  A workgroup size (0: the kernels' own) is a
+// parameter of those two only, so with one given the choice is between them.
+hipError_t launch_variant(int variant, const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks,
+                          hipStream_t stream, uint32_t threads = 0) {
+    if (variant == TDES_VARIANT_AUTO && threads == 0) return tdes::launch_auto(ks, in, out, n_blocks, stream);
+    const bool table = variant == TDES_VARIANT_TABLE || (variant == TDES_VARIANT_AUTO && n_blocks < tdes::kAutoTableBelow);
+    return table ? tdes::launch_table(ks, in, out, n_blocks, stream, threads)
+                 : tdes::launch_bitslice(ks, in, out, n_blocks, stream, threads);
 }
 
 }  // namespace
@@ -81,16 +86,7 @@ extern "C" int tdes_ecb_run(const void *dev_sched, const void *in, void *out, ui
     const uint8_t *src = static_cast<const uint8_t *>(in);
     uint8_t *dst = static_cast<uint8_t *>(out);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    hipError_t err;
-    switch (resolve_variant(variant, n_blocks)) {
-        case TDES_VARIANT_BITSLICE:
-            err = tdes::launch_bitslice(ks, src, dst, n_blocks, s);
-            break;
-        default:
-            err = tdes::launch_table(ks, src, dst, n_blocks, s);
-            break;
-    }
-    return err == hipSuccess ? TDES_OK : TDES_ERR_HIP;
+    return launch_variant(variant, ks, src, dst, n_blocks, s) == hipSuccess ? TDES_OK : TDES_ERR_HIP;
 }
 
 extern "C" int tdes_ecb_encrypt(const void *dev_sched, const void *in, void *out, uint64_t n_blocks, void *stream) {
@@ -117,10 +113,8 @@ extern "C" int tdes_ecb_chunked(const void *dev_sched, const void *in, void *out
     hipStream_t s = static_cast<hipStream_t>(stream);
     for (uint64_t first = 0; first < n_blocks; first += chunk_blocks) {
         const uint64_t n = n_blocks - first < chunk_blocks ? n_blocks - first : chunk_blocks;
-        const hipError_t e = resolve_variant(variant, n) == TDES_VARIANT_BITSLICE
-                                 ? tdes::launch_bitslice(ks, src + 8 * first, dst + 8 * first, n, s, threads)
-                                 : tdes::launch_table(ks, src + 8 * first, dst + 8 * first, n, s, threads);
-        if (e != hipSuccess) return TDES_ERR_HIP;
+        if (launch_variant(variant, ks, src + 8 * first, dst + 8 * first, n, s, threads) != hipSuccess)
+            return TDES_ERR_HIP;
     }
     return TDES_OK;
 }

@@ -54,7 +54,18 @@ hipError_t launch_table(const uint32_t *ks, const uint8_t *in, uint8_t *out, uin
                         hipStream_t stream, uint32_t threads = 0);
 hipError_t launch_bitslice(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks,
                            hipStream_t stream, uint32_t threads = 0);
-// TDES_VARIANT_AUTO: the table kernel below this many blocks, the bitsliced one from it on.
+// Short messages (k_short.hip); n_blocks below kShortModesBelow.
+hipError_t launch_short_ecb(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, hipStream_t stream);
+hipError_t launch_short_ctr(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, uint64_t iv,
+                            hipStream_t stream);
+hipError_t launch_short_cbc_decrypt(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, uint64_t iv,
+                                    hipStream_t stream);
+// TDES_VARIANT_AUTO, by blocks: the one-bit-per-lane kernel below kShortBelow (its time grows by 0.29 us
+// per 1024 blocks from 4.4 us at 8192 and meets the table kernel's 6.4 us at about 15000), the table
+// kernel below kAutoTableBelow, the bitsliced one from it on.  The modes have no table kernel; the
+// bitsliced one takes 36 us for any short message (72 us with a partial last tile).
+constexpr uint64_t kShortBelow = 14336;
+constexpr uint64_t kShortModesBelow = 1ull << 16;
 constexpr uint64_t kAutoTableBelow = 1ull << 20;
 hipError_t launch_auto(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, hipStream_t stream);
 // Block-parallel modes (bitsliced): ks is the encryption half for CTR and the
