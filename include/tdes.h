@@ -107,10 +107,10 @@ int tdes_ecb_encrypt(const void *dev_sched, const void *in, void *out, uint64_t 
 int tdes_ecb_decrypt(const void *dev_sched, const void *in, void *out, uint64_t n_blocks, void *stream);
 
 /*
- * Kernel variants.  TDES_VARIANT_AUTO is the shipped default: the faster one on
- * MI355X for the message's size, the table kernel below 2^20 blocks (its
- * latency is lower) and the bitsliced kernel from there on (its throughput is
- * about three times higher).
+ * Kernel variants.  TDES_VARIANT_AUTO is the shipped default: the fastest
+ * kernel on MI355X for the message's size.  Short messages take one bit of the
+ * round function per lane, then come the table kernel, a workgroup per tile of
+ * 2048 blocks, and from about 2^21 blocks on the bitsliced kernel.
  */
 #define TDES_VARIANT_AUTO 0
 #define TDES_VARIANT_TABLE 1    /* combined S-box/P tables in LDS, one block per lane */
@@ -128,7 +128,8 @@ int tdes_ecb_run(const void *dev_sched, const void *in, void *out, uint64_t n_bl
  * tdes_ecb_run, issued as consecutive launches of chunk_blocks blocks each
  * (the last one shorter), all on `stream`, each with `variant`
  * (TDES_VARIANT_AUTO chooses by the chunk's size) and workgroups of `threads`
- * threads (0: the kernels' own, 256; else 64, 128, 256, 512 or 1024).  It
+ * threads (0: the kernels' own; else 64, 128, 256, 512 or 1024, and then
+ * TDES_VARIANT_AUTO chooses between the table and the bitsliced kernel).  It
  * exists to measure the paper's two launch parameters on this GPU: threads per
  * workgroup (Table I) and blocks per launch (Table II).  Every launch pays the
  * launch overhead and the kernel's latency, which dominate for small chunks;
@@ -170,7 +171,7 @@ int tdes_cbc_decrypt(const void *dev_sched, const uint8_t iv[8], const void *in,
  * ECB over a message held in host memory (the paper's setting, Listing 1.1,
  * with the transfers overlapped instead of done once around the kernels):
  * chunks of chunk_blocks blocks move through three device buffers; the copy
- * in, the bitsliced kernel and the copy out each run on their own stream so
+ * in, the kernel (TDES_VARIANT_AUTO) and the copy out each run on their own stream so
  * that chunks overlap.  Synchronous: returns when host_out holds the result
  * (work already queued on `stream` is waited for first).  Allocates
  * 3 * chunk_blocks * 8 bytes of device memory for the duration of the call.

@@ -10,8 +10,9 @@ namespace tdes {
 
 hipError_t launch_auto(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, hipStream_t stream) {
     if (n_blocks < kShortBelow) return launch_short_ecb(ks, in, out, n_blocks, stream);
-    return n_blocks < kAutoTableBelow ? launch_table(ks, in, out, n_blocks, stream)
-                                      : launch_bitslice(ks, in, out, n_blocks, stream);
+    if (n_blocks < kAutoTableBelow) return launch_table(ks, in, out, n_blocks, stream);
+    if (n_blocks < kTeamBelow) return launch_team_ecb(ks, in, out, n_blocks, stream);
+    return launch_bitslice(ks, in, out, n_blocks, stream);
 }
 
 namespace {
@@ -56,18 +57,14 @@ int check_buffers(const void *dev_sched, const void *in, const void *out, uint64
     return TDES_OK;
 }
 
-// One launch of a variant.  The automatic choice (internal.h), on MI355X measurements of one launch
-// (encrypt, HIP events around the launch): the bitsliced kernel costs about 36 us for
-// anything up to 2^18 blocks (one wave runs a whole 2048-block tile through all
-// 48 rounds) and then scales at about 900 GB/s; the table kernel costs 8-13 us
-// up to 2^16 blocks (14 us at 2^18; the spread is the launch cost of different
-// machines) and scales at about 260 GB/s.  At 2^20 blocks the bitsliced kernel
-// is already ahead (39 vs 42 us).  A workgroup size (0: the kernels' own) is a
-// parameter of those two only, so with one given the choice is between them.
+// One launch of a variant.  The automatic choice is launch_auto's (internal.h).  A workgroup size (0: the
+// kernels' own) is a parameter of the table and the bitsliced kernel only, so with one given the choice
+// is between those two: at 2^20 blocks the bitsliced one is ahead (34 vs 35 us), below it the table kernel.
+constexpr uint64_t kThreadsTableBelow = 1ull << 20;
 hipError_t launch_variant(int variant, const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks,
                           hipStream_t stream, uint32_t threads = 0) {
     if (variant == TDES_VARIANT_AUTO && threads == 0) return tdes::launch_auto(ks, in, out, n_blocks, stream);
-    const bool table = variant == TDES_VARIANT_TABLE || (variant == TDES_VARIANT_AUTO && n_blocks < tdes::kAutoTableBelow);
+    const bool table = variant == TDES_VARIANT_TABLE || (variant == TDES_VARIANT_AUTO && n_blocks < kThreadsTableBelow);
     return table ? tdes::launch_table(ks, in, out, n_blocks, stream, threads)
                  : tdes::launch_bitslice(ks, in, out, n_blocks, stream, threads);
 }

@@ -29,12 +29,12 @@ constexpr int kTileBlocks = 32 * kLanes;     // blocks per wave tile
 // the rate of v_bitop3 with vector-register operands, of adds and of right shifts
 // (measured), so the selects are v_bitop3 with the mask in a vector register and a
 // 1-bit left shift is an add.
-template <int S, uint32_t M>
-__device__ __forceinline__ void exchange_stage(uint32_t (&w)[32]) {
+template <int S, uint32_t M, int N>
+__device__ __forceinline__ void exchange_stage(uint32_t (&w)[N]) {
     uint32_t m;
     asm("v_mov_b32 %0, %1" : "=v"(m) : "i"(M));
 #pragma unroll
-    for (int j = 0; j < 32; j++) {
+    for (int j = 0; j < N; j++) {
         if (j & S) continue;
         const uint32_t a = w[j], b = w[j + S];
         uint32_t bs;
@@ -47,6 +47,27 @@ __device__ __forceinline__ void exchange_stage(uint32_t (&w)[32]) {
     }
 }
 
+// The stages within bytes and within half-words.  On 8 (16) words: afterwards bit j of byte (half-word) c
+// of w[i] is what bit i of byte (half-word) c of w[j] was.
+template <int N>
+__device__ __forceinline__ void transpose8(uint32_t (&w)[N]) {
+    exchange_stage<4, 0x0F0F0F0Fu>(w);
+    exchange_stage<2, 0x33333333u>(w);
+    exchange_stage<1, 0x55555555u>(w);
+}
+
+template <int N>
+__device__ __forceinline__ void transpose16(uint32_t (&w)[N]) {
+#pragma unroll
+    for (int j = 0; j < N; j++) {
+        if (j & 8) continue;
+        const uint32_t a = w[j], b = w[j + 8];
+        w[j] = __builtin_amdgcn_perm(b, a, 0x06020400u);       // bytes a0 b0 a2 b2
+        w[j + 8] = __builtin_amdgcn_perm(b, a, 0x07030501u);   // bytes a1 b1 a3 b3
+    }
+    transpose8(w);
+}
+
 // In place: afterwards bit j of w[i] is what bit i of w[j] was.
 __device__ __forceinline__ void transpose32(uint32_t (&w)[32]) {
 #pragma unroll
@@ -55,16 +76,7 @@ __device__ __forceinline__ void transpose32(uint32_t (&w)[32]) {
         w[j] = __builtin_amdgcn_perm(b, a, 0x05040100u);       // a.lo16 | b.lo16 << 16
         w[j + 16] = __builtin_amdgcn_perm(b, a, 0x07060302u);  // a.hi16 | b.hi16 << 16
     }
-#pragma unroll
-    for (int j = 0; j < 32; j++) {
-        if (j & 8) continue;
-        const uint32_t a = w[j], b = w[j + 8];
-        w[j] = __builtin_amdgcn_perm(b, a, 0x06020400u);       // bytes a0 b0 a2 b2
-        w[j + 8] = __builtin_amdgcn_perm(b, a, 0x07030501u);   // bytes a1 b1 a3 b3
-    }
-    exchange_stage<4, 0x0F0F0F0Fu>(w);
-    exchange_stage<2, 0x33333333u>(w);
-    exchange_stage<1, 0x55555555u>(w);
+    transpose16(w);
 }
 
 // ---- rounds ----

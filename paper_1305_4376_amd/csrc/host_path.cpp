@@ -81,7 +81,7 @@ extern "C" int tdes_ecb_host(const void *dev_sched, const void *host_in, void *h
         if ((c >= kSlots && hipStreamWaitEvent(p.in, p.freed[s], 0) != hipSuccess) ||
             hipMemcpyAsync(p.slot[s], src + 8 * first, n * 8, hipMemcpyHostToDevice, p.in) != hipSuccess ||
             hipEventRecord(p.loaded[s], p.in) != hipSuccess || hipStreamWaitEvent(p.work, p.loaded[s], 0) != hipSuccess ||
-            tdes::launch_bitslice(ks, p.slot[s], p.slot[s], n, p.work) != hipSuccess ||
+            tdes::launch_auto(ks, p.slot[s], p.slot[s], n, p.work) != hipSuccess ||
             hipEventRecord(p.done[s], p.work) != hipSuccess || hipStreamWaitEvent(p.out, p.done[s], 0) != hipSuccess ||
             hipMemcpyAsync(dst + 8 * first, p.slot[s], n * 8, hipMemcpyDeviceToHost, p.out) != hipSuccess ||
             hipEventRecord(p.freed[s], p.out) != hipSuccess)

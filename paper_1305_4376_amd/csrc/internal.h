@@ -54,19 +54,30 @@ hipError_t launch_table(const uint32_t *ks, const uint8_t *in, uint8_t *out, uin
                         hipStream_t stream, uint32_t threads = 0);
 hipError_t launch_bitslice(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks,
                            hipStream_t stream, uint32_t threads = 0);
-// Short messages (k_short.hip); n_blocks below kShortModesBelow.
+// Short messages (k_short.hip): one bit of f per lane.  n_blocks below 2^32.
 hipError_t launch_short_ecb(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, hipStream_t stream);
 hipError_t launch_short_ctr(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, uint64_t iv,
                             hipStream_t stream);
 hipError_t launch_short_cbc_decrypt(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, uint64_t iv,
                                     hipStream_t stream);
-// TDES_VARIANT_AUTO, by blocks: the one-bit-per-lane kernel below kShortBelow (its time grows by 0.29 us
-// per 1024 blocks from 4.4 us at 8192 and meets the table kernel's 6.4 us at about 15000), the table
-// kernel below kAutoTableBelow, the bitsliced one from it on.  The modes have no table kernel; the
-// bitsliced one takes 36 us for any short message (72 us with a partial last tile).
+// Middling messages (k_team.hip): a workgroup per tile of 2048 blocks.  n_blocks below 2^42.
+hipError_t launch_team_ecb(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, hipStream_t stream);
+hipError_t launch_team_ctr(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, uint64_t iv,
+                           hipStream_t stream);
+hipError_t launch_team_cbc_decrypt(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, uint64_t iv,
+                                   hipStream_t stream);
+// TDES_VARIANT_AUTO by message length, from launches back to back on MI355X:
+//   below kShortBelow      one bit of f per lane: 3.0 us to 2048 blocks, 4.4 at 8192, then 0.29 us per 1024;
+//                          meets the table kernel's 6.2 us at about 14500;
+//   below kAutoTableBelow  the table kernel: 6.2 us to 2^16 blocks, 6.7 at 2^17, 9.9 at 2^18, 16.2 at 3 * 2^17,
+//                          where the team takes 15.0 (14.8 from the shortest message on);
+//   below kTeamBelow       a team per tile: 30.6 us at 2^21 and 43 at 3 * 2^20, one wave per tile 35.1 and 39.2;
+//   from there on          one wave per tile.
+// The modes have no table kernel: one bit per lane meets the team's 14.8 us at about 46000 blocks.
 constexpr uint64_t kShortBelow = 14336;
-constexpr uint64_t kShortModesBelow = 1ull << 16;
-constexpr uint64_t kAutoTableBelow = 1ull << 20;
+constexpr uint64_t kShortModesBelow = 45056;
+constexpr uint64_t kAutoTableBelow = 5ull << 16;
+constexpr uint64_t kTeamBelow = 9ull << 18;
 hipError_t launch_auto(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, hipStream_t stream);
 // Block-parallel modes (bitsliced): ks is the encryption half for CTR and the
 // decryption half for CBC decryption; iv is the 8 IV bytes read as a big-endian integer.

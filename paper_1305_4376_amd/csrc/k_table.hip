@@ -38,7 +38,10 @@
 
 namespace {
 
-constexpr int kDefaultThreads = 256;
+// Threads per workgroup: more waves share a workgroup's tables and hide the round's chain, fewer start
+// sooner.  256 / 512 / 1024 threads: 2^14 blocks 6.1 / 6.3 / 9.1 us, 2^16 6.4 / 6.5 / 9.2, 2^17 7.2 / 6.7 /
+// 9.3, 2^18 11.1 / 9.9 / 9.5, 2^19 19.0 / 16.6 / 16.1, 3 * 2^18 27.3 / 21.9 / 26.7.
+constexpr uint32_t default_threads(uint64_t n_blocks) { return n_blocks <= 1u << 16 ? 256 : 512; }
 constexpr int kCopies = 32;
 
 constexpr uint32_t rotl32(uint32_t x, int n) { return n == 0 ? x : (x << n) | (x >> (32 - n)); }
@@ -237,7 +240,7 @@ hipError_t launch_table(const uint32_t *ks, const uint8_t *in, uint8_t *out, uin
                         hipStream_t stream, uint32_t threads) {
     DeviceInfo info;
     if (device_info(&info) != TDES_OK) return hipErrorInvalidDevice;
-    if (threads == 0) threads = kDefaultThreads;
+    if (threads == 0) threads = default_threads(n_blocks);
     // 64 KiB of LDS per workgroup: two per CU (the compiler fits the registers of every size to that)
     const uint64_t resident = (uint64_t)info.cu_count * 2;
     // One block per lane while one pass of the resident grid covers the message, else two.
