@@ -333,14 +333,13 @@ __device__ __forceinline__ uint32_t be_lo_word(uint64_t v) { return __builtin_bs
 // A wave tile: 2048 consecutive blocks starting at `tin`/`tout` (wave-uniform),
 // blocks first_block.. of the message; lane l holds blocks 128k + 2l and
 // 128k + 2l + 1 (k = 0..15), so each access is 16 bytes per lane over 1 KiB
-// contiguous across the wave.  kFull: all 2048 blocks valid and both buffers
-// 16-byte aligned.  Otherwise (n_valid < 2048, or buffers only 8-byte
-// aligned) each block is loaded and stored on its own, at the same
-// addresses, only if it is one of the first n_valid; lanes past the end
-// compute on zeros.  Whole-tile loads and stores are nontemporal (every block
+// contiguous across the wave.  kFull: all 2048 blocks valid.  Otherwise each
+// block is loaded and stored on its own, at the same addresses, only if it is
+// one of the first n_valid; lanes past the end compute on zeros.  Buffers are
+// 8-byte aligned; the hardware takes 16-byte accesses at any 4-byte address.  Whole-tile loads and stores are nontemporal (every block
 // is read and written once), except CBC decryption's first read, which is read
 // again after the rounds.
-typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+typedef unsigned int v4u __attribute__((ext_vector_type(4), aligned(8)));
 
 template <TileMode kMode, bool kFull>
 __device__ __forceinline__ void mode_tile(const uint32_t *__restrict__ ks, const uint8_t *tin, uint8_t *tout,

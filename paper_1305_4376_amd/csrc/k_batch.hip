@@ -105,9 +105,7 @@ TDES_BATCH_KERNEL(const uint32_t *__restrict__ sched, const tdes::PlanHeader *__
                 const uint32_t *ks = sched + __builtin_amdgcn_readfirstlane(sl.ks_off);
                 const uint8_t *tin = base + in_off;
                 uint8_t *tout = base + out_off;
-                const bool full = cnt == kTileBlocks &&
-                                  ((reinterpret_cast<uintptr_t>(tin) | reinterpret_cast<uintptr_t>(tout)) & 15) == 0;
-                if (full)
+                if (cnt == kTileBlocks)
                     wave_tile<true>(ks, tin, tout, kTileBlocks, lane);
                 else
                     wave_tile<false>(ks, tin, tout, cnt, lane);

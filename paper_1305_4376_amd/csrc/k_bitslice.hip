@@ -7,13 +7,14 @@
 // tables and no LDS, a fixed data-independent cost per block, and the three
 // DES stages of EDE fused in one pass over the data.
 //
-// Two kernels.  The main one takes every whole 2048-block tile (16 KiB of the
-// message, one wave each) of a message whose buffers are 16-byte aligned; its
-// code has only that path, so it fits 128 VGPRs and runs four waves per SIMD.
-// The tail kernel takes the last partial tile, or every tile when a buffer is
-// only 8-byte aligned, with per-block loads and stores.  Tiles beyond 2^22
-// per launch loop grid-stride.  The key is the same for the whole launch, so
-// its masks come from scalar registers.
+// The kernel takes every whole 2048-block tile (16 KiB of the message, one
+// wave each); its code has only that path, so it fits 128 VGPRs and runs four
+// waves per SIMD.  Tiles beyond 2^22 per launch loop grid-stride.  A partial
+// last tile follows in the short-message kernel (k_short.hip): 3 us, where a
+// wave alone on it would take 33.  Buffers that are only 8-byte aligned take
+// the same path (3000001 blocks behind an 8-byte header: 43.4 us a call with
+// per-block accesses, 43.2 now, 3 of it the tail).  The key is the same for the whole launch,
+// so its masks come from scalar registers.
 #include <hip/hip_runtime.h>
 
 #include "bitslice_core.h"
@@ -44,25 +45,6 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void tdes_bitslice_kernel(
     }
 }
 
-// Tiles first_tile.. of the message, any of them partial; 8-byte alignment suffices.
-template <TileMode kMode, int kThreads = kDefaultThreads>
-__global__ __launch_bounds__(kThreads) void tdes_bitslice_tail_kernel(const uint32_t *__restrict__ ks,
-                                                                      const uint8_t *in, uint8_t *out,
-                                                                      uint64_t first_tile, uint64_t n_blocks,
-                                                                      uint64_t iv) {
-    constexpr int kWaves = kThreads / kLanes;
-    const uint32_t lane = threadIdx.x % kLanes;
-    const uint64_t tiles = (n_blocks + kTileBlocks - 1) / kTileBlocks;
-    const uint64_t stride = (uint64_t)gridDim.x * kWaves;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
-    for (uint64_t tile = first_tile + (uint64_t)blockIdx.x * kWaves + wave; tile < tiles; tile += stride) {
-        const uint64_t first = tile * kTileBlocks;
-        const uint64_t left = n_blocks - first;
-        const uint32_t n_valid = left < kTileBlocks ? (uint32_t)left : kTileBlocks;
-        mode_tile<kMode, false>(ks, in + 8 * first, out + 8 * first, n_valid, lane, first, iv);
-    }
-}
-
 uint32_t grid_for(uint64_t tiles, int waves_per_group) {
     const uint64_t g = (tiles + waves_per_group - 1) / waves_per_group;
     return (uint32_t)(g < kMaxGrid ? g : kMaxGrid);
@@ -72,21 +54,24 @@ template <TileMode kMode, int kThreads = kDefaultThreads>
 hipError_t launch(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, uint64_t iv,
                   hipStream_t stream) {
     constexpr int kWaves = kThreads / kLanes;
-    const bool vec16 = ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
-    const uint64_t whole = vec16 ? n_blocks / kTileBlocks : 0;
+    const uint64_t whole = n_blocks / kTileBlocks, done = whole * kTileBlocks;
     if (whole) {
         hipLaunchKernelGGL((tdes_bitslice_kernel<kMode, kThreads>), dim3(grid_for(whole, kWaves)), dim3(kThreads), 0,
                            stream, ks, in, out, whole, iv);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (whole * kTileBlocks < n_blocks) {
-        const uint64_t rest = (n_blocks - whole * kTileBlocks + kTileBlocks - 1) / kTileBlocks;
-        hipLaunchKernelGGL((tdes_bitslice_tail_kernel<kMode, kThreads>), dim3(grid_for(rest, kWaves)), dim3(kThreads),
-                           0, stream, ks, in, out, whole, n_blocks, iv);
-        return hipGetLastError();
-    }
-    return hipSuccess;
+    if (done == n_blocks) return hipSuccess;
+    const uint8_t *tin = in + 8 * done;
+    uint8_t *tout = out + 8 * done;
+    // (Without a whole tile the call asked for the bitsliced rounds by name: a team's are bitsliced too.)
+    if constexpr (kMode == TileMode::kEcb)
+        return whole ? tdes::launch_short_ecb(ks, tin, tout, n_blocks - done, stream)
+                     : tdes::launch_team_ecb(ks, in, out, n_blocks, stream);
+    else if constexpr (kMode == TileMode::kCtr)
+        return tdes::launch_short_ctr(ks, tin, tout, n_blocks - done, iv + done, stream);
+    else
+        return tdes::launch_short_cbc_decrypt(ks, tin, tout, n_blocks - done, done, iv, stream);
 }
 
 }  // namespace
@@ -115,7 +100,7 @@ hipError_t launch_ctr(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint6
 
 hipError_t launch_cbc_decrypt(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, uint64_t iv,
                               hipStream_t stream) {
-    if (n_blocks < kShortModesBelow) return launch_short_cbc_decrypt(ks, in, out, n_blocks, iv, stream);
+    if (n_blocks < kShortModesBelow) return launch_short_cbc_decrypt(ks, in, out, n_blocks, 0, iv, stream);
     if (n_blocks < kTeamBelow) return launch_team_cbc_decrypt(ks, in, out, n_blocks, iv, stream);
     return launch<TileMode::kCbcDecrypt>(ks, in, out, n_blocks, iv, stream);
 }

@@ -84,9 +84,10 @@ __device__ __forceinline__ uint32_t xor_half(uint32_t a, uint64_t f, uint32_t hi
     return __builtin_amdgcn_bitop3_b32(t, (uint32_t)(f >> 32), hi, 0x78);                // t ^ (f.hi & hi)
 }
 
+// continued (CBC decryption): in[0] is not the message's first block.
 template <TileMode kMode>
 __global__ __launch_bounds__(kShortThreads) void tdes_short_kernel(const uint32_t *__restrict__ ks, const uint8_t *in,
-                                                                   uint8_t *out, uint32_t n_blocks, uint64_t iv) {
+                                                                   uint8_t *out, uint32_t n_blocks, bool continued, uint64_t iv) {
     const uint32_t lane = threadIdx.x % kLanes;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
     const uint32_t first = (blockIdx.x * (kShortThreads / kLanes) + wave) * kBlocksPerWave;
@@ -103,7 +104,7 @@ __global__ __launch_bounds__(kShortThreads) void tdes_short_kernel(const uint32_
     uint2 prev;
     if constexpr (kMode == TileMode::kCbcDecrypt) {
         prev = make_uint2(be_hi_word(iv), be_lo_word(iv));
-        if (at != 0) prev = src[-1];
+        if (at != 0 || continued) prev = src[-1];
     }
 
     const uint32_t rot = pos, key = pos >> 8;
@@ -138,28 +139,29 @@ namespace tdes {
 namespace {
 
 template <TileMode kMode>
-hipError_t launch(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, uint64_t iv, hipStream_t stream) {
+hipError_t launch(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, bool continued, uint64_t iv,
+                  hipStream_t stream) {
     constexpr uint32_t per_group = kBlocksPerWave * (kShortThreads / kLanes);
-    const uint32_t n = (uint32_t)n_blocks;  // below kShortBelow
+    const uint32_t n = (uint32_t)n_blocks;
     hipLaunchKernelGGL(tdes_short_kernel<kMode>, dim3((n + per_group - 1) / per_group), dim3(kShortThreads), 0, stream,
-                       ks, in, out, n, iv);
+                       ks, in, out, n, continued, iv);
     return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_short_ecb(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, hipStream_t stream) {
-    return launch<TileMode::kEcb>(ks, in, out, n_blocks, 0, stream);
+    return launch<TileMode::kEcb>(ks, in, out, n_blocks, false, 0, stream);
 }
 
 hipError_t launch_short_ctr(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, uint64_t iv,
                             hipStream_t stream) {
-    return launch<TileMode::kCtr>(ks, in, out, n_blocks, iv, stream);
+    return launch<TileMode::kCtr>(ks, in, out, n_blocks, false, iv, stream);
 }
 
-hipError_t launch_short_cbc_decrypt(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, uint64_t iv,
-                                    hipStream_t stream) {
-    return launch<TileMode::kCbcDecrypt>(ks, in, out, n_blocks, iv, stream);
+hipError_t launch_short_cbc_decrypt(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks,
+                                    uint64_t first, uint64_t iv, hipStream_t stream) {
+    return launch<TileMode::kCbcDecrypt>(ks, in, out, n_blocks, first != 0, iv, stream);
 }
 
 }  // namespace tdes

@@ -155,14 +155,14 @@ __global__ __launch_bounds__(kThreads, kGroupsPerCU) void tdes_static_batch_kern
         const tdes_job &x = jobs[lo];
         const uint64_t n_blocks = uniform64(x.n_blocks);
         const uint64_t first = (uint64_t)(ticket - __builtin_amdgcn_readfirstlane(tile_start[lo])) * kTileBlocks;
-        const uint32_t count = (uint32_t)min((uint64_t)kTileBlocks, n_blocks - first);
+        // (Compared through a shift: the compiler selects min(kTileBlocks, left) by a stale condition bit here.)
+        const uint64_t left = n_blocks - first;
+        const uint32_t count = left / kTileBlocks ? kTileBlocks : (uint32_t)left;
         const uint32_t *ks = sched + (uint64_t)__builtin_amdgcn_readfirstlane(x.sched_idx) * (TDES_SCHED_BYTES / 4) +
                              __builtin_amdgcn_readfirstlane(x.direction) * tdes::kDirWords;
         const uint8_t *tin = base + uniform64(x.in_off) + 8 * first;
         uint8_t *tout = base + uniform64(x.out_off) + 8 * first;
-        const bool full = count == kTileBlocks &&
-                          ((reinterpret_cast<uintptr_t>(tin) | reinterpret_cast<uintptr_t>(tout)) & 15) == 0;
-        if (full)
+        if (count == kTileBlocks)
             wave_tile<true>(ks, tin, tout, kTileBlocks, lane);
         else
             wave_tile<false>(ks, tin, tout, count, lane);

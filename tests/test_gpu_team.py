@@ -1,4 +1,5 @@
-"""GPU parity of the kernel that shares a tile of 2048 blocks between a workgroup's eight waves.
+"""GPU parity of the kernel that shares a tile of 2048 blocks between a workgroup's eight waves, and of
+the switch from it to one wave per tile with a short partial tile behind the whole ones.
 
 Sizes on both sides of its range in each mode, with a whole last tile, one of a single block and one
 that lacks one block or ends inside a row of 64; 16- and 8-byte aligned buffers; a CTR counter that
@@ -30,7 +31,7 @@ def _check(guard, dst, offset, want):
     assert bool((guard[offset + dst.numel():] == 0xA5).all()) and bool((guard[:offset] == 0xA5).all())
 
 
-@pytest.mark.parametrize("n", [327679, 327680, 327681, 331000, 2359295, 2359296])
+@pytest.mark.parametrize("n", [327679, 327680, 327681, 331000, 2359295, 2359296, 2359297, 2361343])
 @pytest.mark.parametrize("offset", [0, 8])
 def test_ecb_around_the_team_range(n, offset):
     print(f"[team] ecb n={n} offset={offset}", flush=True)
@@ -63,3 +64,25 @@ def test_modes_around_the_team_range(n, offset):
     td.tdes_ctr_crypt(sched, iv, src, src)
     torch.cuda.synchronize()
     assert np.array_equal(src.cpu().numpy(), host)
+
+
+@pytest.mark.parametrize("n", [2359295, 2359296, 2359297, 2361343])
+@pytest.mark.parametrize("offset", [0, 8])
+def test_modes_of_long_messages(n, offset):
+    """The first tiles and everything from two tiles before the end: a partial last tile is its own launch."""
+    print(f"[team] long modes n={n} offset={offset}", flush=True)
+    keys, host, sched, src, guard, dst = _case(840 + n % 11, n, offset)
+    at = n // 2048 * 2048 - 4096
+    iv = (2**64 - at - 5000).to_bytes(8, "big")  # the counter wraps near the end
+    td.tdes_ctr_crypt(sched, iv, src, dst)
+    torch.cuda.synchronize()
+    got = dst.cpu().numpy()
+    assert np.array_equal(got[: 8 * 4096], oracle.tdes_ctr(*keys, iv, host[: 8 * 4096]))
+    iv_at = ((int.from_bytes(iv, "big") + at) % 2**64).to_bytes(8, "big")
+    assert np.array_equal(got[8 * at:], oracle.tdes_ctr(*keys, iv_at, host[8 * at:]))
+    td.tdes_cbc_decrypt(sched, iv, src, dst)
+    torch.cuda.synchronize()
+    got = dst.cpu().numpy()
+    assert np.array_equal(got[: 8 * 4096], oracle.tdes_cbc(*keys, iv, host[: 8 * 4096], decrypt=True))
+    assert np.array_equal(got[8 * at:], oracle.tdes_cbc(*keys, host[8 * at - 8: 8 * at].tobytes(), host[8 * at:], decrypt=True))
+    assert bool((guard[offset + 8 * n:] == 0xA5).all()) and bool((guard[:offset] == 0xA5).all())
