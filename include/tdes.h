@@ -219,7 +219,7 @@ typedef struct tdes_batch_info {
 } tdes_batch_info;
 
 /* Flags of tdes_ecb_batch. */
-#define TDES_BATCH_NO_GRAPH 1u     /* launch the kernel directly instead of replaying a graph */
+#define TDES_BATCH_NO_GRAPH 1u     /* tdes_ecb_batch: capture no graph; replay: launch the kernel directly */
 #define TDES_BATCH_PER_MESSAGE 2u  /* baseline: one plain launch per message, automatic variant (no plan, no graph) */
 
 /*
@@ -238,14 +238,15 @@ int tdes_ctx_destroy(tdes_ctx *ctx);
 /*
  * Encrypt or decrypt every message of a batch: ECB on each message as in
  * tdes_ecb_encrypt/decrypt, all messages in one launch of a persistent kernel
- * (replayed from a captured graph unless TDES_BATCH_NO_GRAPH).
+ * (captured in a graph, for tdes_ecb_batch_replay, unless TDES_BATCH_NO_GRAPH).
  *   jobs: host, n_jobs entries; read before the call returns.
  *   dev_sched_table: device, n_scheds schedules written by tdes_sched_upload.
  *   dev_base: device; every offset is relative to it.
  * The host checks every job first: direction and schedule index, alignment,
  * and that no message writes bytes another message reads or writes (only
- * exact in-place is allowed).  The plan is copied to the device on `stream`;
- * the call can block until the previous batch's copy has been read.
+ * exact in-place is allowed).  The plan is written on the device by a kernel
+ * on `stream`; the call can block until the previous batch's has run.  A batch
+ * of few tiles shares each of them between the waves of a workgroup.
  * Errors: TDES_ERR_NULL, TDES_ERR_ARG, TDES_ERR_ALIGN, TDES_ERR_SIZE,
  * TDES_ERR_OVERLAP, TDES_ERR_NOMEM, TDES_ERR_HIP.
  */

@@ -12,12 +12,15 @@
 // instead; lane slots from all messages are packed 64 to a lane tile, where
 // each lane has its own key.  A 2048-block
 // tile then never runs mostly empty for short messages.  Lane tiles go first
-// so that the cheaper wave tiles fill the tail of the launch.
+// so that the cheaper wave tiles fill the tail of the launch.  The host only
+// counts: it leaves one record per message in pinned memory, and a kernel
+// (k_plan.hip) writes the slots on the device.
 //
-// Graphs.  The kernel reads the tile count from the uploaded plan, so one
+// Graphs.  The kernels read the tile count from the plan's header, so one
 // captured graph (a single kernel node) serves every batch with the same
 // base pointer, schedule table and launch shape; it is captured on a private
-// stream and replayed on the caller's.
+// stream and replayed on the caller's by tdes_ecb_batch_replay.  Batches of few tiles have a kernel,
+// and a graph, of their own.
 #include <stdint.h>
 #include <stdlib.h>
 #include <string.h>
@@ -49,11 +52,11 @@ struct tdes_ctx {
     int cu_count = 0;
     hipStream_t capture_stream = nullptr;
     uint32_t *d_counter = nullptr;
-    // Plan buffers: device and pinned host staging with the same layout.
+    // The plan: the messages' records in pinned host memory, the header and slots on the device.
     uint8_t *d_plan = nullptr;
-    uint8_t *h_plan = nullptr;
-    size_t cap_tiles = 0, cap_slots = 0;
-    hipEvent_t staging_free = nullptr;  // the last upload has read the staging buffer
+    tdes::PlanMessage *h_plan = nullptr;
+    size_t cap_slots = 0, cap_messages = 0;
+    hipEvent_t staging_free = nullptr;  // the last plan kernel has read the records
     hipEvent_t plan_done = nullptr;     // the last kernel has finished with the device plan
     bool have_plan = false;
     // Last planned batch (for replay).
@@ -66,50 +69,58 @@ struct tdes_ctx {
     uint32_t wave_remainder = kDefaultWaveRemainder;  // remainders this long take a wave tile
     uint32_t tiles_per_draw = 1;                      // tiles a wave takes per counter draw
     bool capped = false;                              // launch the 120-VGPR kernel variant
-    // Captured graph and what it was captured for.
-    hipGraphExec_t exec = nullptr;
-    const void *g_sched = nullptr;
-    const void *g_base = nullptr;
-    const void *g_tiles = nullptr;  // every pointer the kernel node was captured with
-    const void *g_slots = nullptr;
-    uint32_t g_grid = 0, g_threads = 0, g_draw = 0;
-    bool g_capped = false;
+    // Captured graphs (one wave per tile; a workgroup per tile) and everything their kernel nodes were captured with.
+    struct Graph {
+        hipGraphExec_t exec = nullptr;
+        const void *sched = nullptr, *base = nullptr, *plan = nullptr;
+        uint32_t grid = 0, threads = 0, draw = 0;
+        bool capped = false;
+
+        void drop() {
+            if (exec) (void)hipGraphExecDestroy(exec);
+            exec = nullptr;
+        }
+    } graphs[2];
     tdes_batch_info info{};
 };
 
 namespace {
 
-size_t slots_offset(size_t cap_tiles) { return 256 + align256(cap_tiles * 4); }
-size_t plan_bytes(size_t cap_tiles, size_t cap_slots) { return slots_offset(cap_tiles) + cap_slots * sizeof(tdes::Slot); }
-
-int ensure_capacity(tdes_ctx *c, size_t tiles, size_t slots) {
-    if (tiles <= c->cap_tiles && slots <= c->cap_slots && c->d_plan) return TDES_OK;
-    size_t nt = std::max<size_t>(tiles, std::max<size_t>(1024, c->cap_tiles * 2));
-    size_t ns = std::max<size_t>(slots, std::max<size_t>(8192, c->cap_slots * 2));
-    // The old buffers may still be in use by an upload or a kernel.
-    if (c->d_plan) {
-        if (hipEventSynchronize(c->plan_done) != hipSuccess) return TDES_ERR_HIP;
-        if (hipEventSynchronize(c->staging_free) != hipSuccess) return TDES_ERR_HIP;
-        // The captured graph points into the old buffer (and at the old slot offset, which
-        // moves with the capacity even if the allocator returns the same address): drop it.
-        if (c->exec) {
-            (void)hipGraphExecDestroy(c->exec);
-            c->exec = nullptr;
-        }
-        (void)hipFree(c->d_plan);
-        (void)hipHostFree(c->h_plan);
-        c->d_plan = c->h_plan = nullptr;
-        c->have_plan = false;
-    }
-    const size_t bytes = plan_bytes(nt, ns);
-    if (hipMalloc(&c->d_plan, bytes) != hipSuccess) { c->d_plan = nullptr; return TDES_ERR_NOMEM; }
-    if (hipHostMalloc(&c->h_plan, bytes, hipHostMallocDefault) != hipSuccess) {
-        (void)hipFree(c->d_plan);
-        c->d_plan = c->h_plan = nullptr;
+// Room for n_messages records; the last plan kernel has read the old ones on return.
+int ensure_records(tdes_ctx *c, size_t n_messages) {
+    // The records must not change under a previous plan kernel.
+    if (hipEventSynchronize(c->staging_free) != hipSuccess) return TDES_ERR_HIP;
+    if (n_messages <= c->cap_messages) return TDES_OK;
+    const size_t n = std::max<size_t>(n_messages, std::max<size_t>(1024, c->cap_messages * 2));
+    if (c->h_plan) (void)hipHostFree(c->h_plan);
+    c->h_plan = nullptr;
+    c->cap_messages = 0;
+    if (hipHostMalloc(&c->h_plan, n * sizeof(tdes::PlanMessage), hipHostMallocDefault) != hipSuccess) {
+        c->h_plan = nullptr;
         return TDES_ERR_NOMEM;
     }
-    c->cap_tiles = nt;
-    c->cap_slots = ns;
+    c->cap_messages = n;
+    return TDES_OK;
+}
+
+// Room for n_slots slots on the device.
+int ensure_slots(tdes_ctx *c, size_t n_slots) {
+    if (n_slots <= c->cap_slots && c->d_plan) return TDES_OK;
+    const size_t n = std::max<size_t>(n_slots, std::max<size_t>(8192, c->cap_slots * 2));
+    if (c->d_plan) {
+        // The old buffer may still be in use by a kernel, and the captured graphs point into it.
+        if (hipEventSynchronize(c->plan_done) != hipSuccess) return TDES_ERR_HIP;
+        for (auto &g : c->graphs) g.drop();
+        (void)hipFree(c->d_plan);
+        c->d_plan = nullptr;
+        c->have_plan = false;
+        c->cap_slots = 0;
+    }
+    if (hipMalloc(&c->d_plan, sizeof(tdes::PlanHeader) + n * sizeof(tdes::Slot)) != hipSuccess) {
+        c->d_plan = nullptr;
+        return TDES_ERR_NOMEM;
+    }
+    c->cap_slots = n;
     return TDES_OK;
 }
 
@@ -154,116 +165,86 @@ int validate_jobs(const tdes_job *jobs, uint32_t n_jobs, uint64_t n_scheds, uint
     return TDES_OK;
 }
 
-// Fills the staging buffer; returns the tile and slot counts.
-void plan_jobs(tdes_ctx *c, const tdes_job *jobs, uint32_t n_jobs, uint32_t *n_tiles_out, uint32_t *n_slots_out,
-               tdes_batch_info *info) {
-    std::vector<tdes::Slot> lane, wave;
+struct Plan {
+    uint32_t messages = 0;        // records written
+    uint64_t wave = 0, lane = 0;  // slots
     uint64_t blocks = 0;
+    uint32_t max_wave = 0;        // wave tiles of the longest message
+
+    uint64_t lane_tiles() const { return (lane + kLanesPerTile - 1) / kLanesPerTile; }
+    uint64_t tiles() const { return lane_tiles() + wave; }
+    uint64_t slots() const { return lane_tiles() * kLanesPerTile + wave; }
+};
+
+// Writes the records of a batch (there is room for n_jobs).  TDES_ERR_SIZE if it has too many slots.
+int plan_jobs(tdes_ctx *c, const tdes_job *jobs, uint32_t n_jobs, Plan *plan) {
+    Plan p;
     for (uint32_t j = 0; j < n_jobs; j++) {
         const tdes_job &x = jobs[j];
-        const uint32_t ks_off = x.sched_idx * (TDES_SCHED_BYTES / 4) + x.direction * tdes::kDirWords;
-        blocks += x.n_blocks;
-        const uint64_t full = x.n_blocks / kWaveBlocks;
+        if (x.n_blocks == 0) continue;
         const uint32_t rem = (uint32_t)(x.n_blocks % kWaveBlocks);
-        for (uint64_t t = 0; t < full; t++)
-            wave.push_back({x.in_off + t * kWaveBlocks * 8, x.out_off + t * kWaveBlocks * 8, kWaveBlocks, ks_off, 0});
-        if (rem == 0) continue;
-        const uint64_t at = full * kWaveBlocks * 8;
-        if (rem >= c->wave_remainder) {
-            wave.push_back({x.in_off + at, x.out_off + at, rem, ks_off, 0});
-            continue;
-        }
-        for (uint32_t s = 0; s < rem; s += kLaneBlocks)
-            lane.push_back({x.in_off + at + 8ull * s, x.out_off + at + 8ull * s, std::min(kLaneBlocks, rem - s),
-                            ks_off, 0});
+        const bool wave_rem = rem >= c->wave_remainder;
+        const uint64_t wave = x.n_blocks / kWaveBlocks + wave_rem;
+        tdes::PlanMessage &m = c->h_plan[p.messages++];
+        m.in_off = x.in_off;
+        m.out_off = x.out_off;
+        m.n_blocks = x.n_blocks;
+        m.ks_off = x.sched_idx * (TDES_SCHED_BYTES / 4) + x.direction * tdes::kDirWords;
+        m.wave_first = (uint32_t)p.wave;
+        m.lane_first = (uint32_t)p.lane;
+        m.wave_tiles = (uint32_t)wave;
+        p.wave += wave;
+        if (!wave_rem) p.lane += (rem + kLaneBlocks - 1) / kLaneBlocks;
+        p.blocks += x.n_blocks;
+        p.max_wave = std::max(p.max_wave, m.wave_tiles);
+        if (p.slots() >= 1ull << 31) return TDES_ERR_SIZE;
     }
-    const uint32_t lane_tiles = (uint32_t)((lane.size() + kLanesPerTile - 1) / kLanesPerTile);
-    lane.resize((size_t)lane_tiles * kLanesPerTile, tdes::Slot{0, 0, 0, 0, 0});  // idle lanes
-    const uint32_t n_slots = (uint32_t)(lane.size() + wave.size());
-    const uint32_t n_tiles = lane_tiles + (uint32_t)wave.size();
-    // Callers have made room: ensure_capacity ran with upper bounds.
-    tdes::PlanHeader *hdr = reinterpret_cast<tdes::PlanHeader *>(c->h_plan);
-    uint32_t *tiles = reinterpret_cast<uint32_t *>(c->h_plan + 256);
-    tdes::Slot *slots = reinterpret_cast<tdes::Slot *>(c->h_plan + slots_offset(c->cap_tiles));
-    memset(hdr, 0, sizeof *hdr);
-    hdr->n_tiles = n_tiles;
-    hdr->n_slots = n_slots;
-    for (uint32_t t = 0; t < lane_tiles; t++) tiles[t] = (t * kLanesPerTile) | tdes::kLaneTileBit;
-    for (size_t w = 0; w < wave.size(); w++) tiles[lane_tiles + w] = (uint32_t)(lane.size() + w);
-    if (!lane.empty()) memcpy(slots, lane.data(), lane.size() * sizeof(tdes::Slot));
-    if (!wave.empty()) memcpy(slots + lane.size(), wave.data(), wave.size() * sizeof(tdes::Slot));
-    *n_tiles_out = n_tiles;
-    *n_slots_out = n_slots;
-    info->tiles = n_tiles;
-    info->wave_tiles = wave.size();
-    info->lane_tiles = lane_tiles;
-    info->slots = n_slots;
-    info->blocks = blocks;
-    info->padded_blocks = (uint64_t)n_tiles * kWaveBlocks;
-}
-
-// Upper bounds of tiles and slots for capacity, before planning.
-void count_bounds(const tdes_job *jobs, uint32_t n_jobs, uint32_t wave_remainder, size_t *tiles, size_t *slots) {
-    size_t wave = 0, lane = 0;
-    for (uint32_t j = 0; j < n_jobs; j++) {
-        const uint64_t n = jobs[j].n_blocks;
-        const uint32_t rem = (uint32_t)(n % kWaveBlocks);
-        wave += n / kWaveBlocks + (rem >= wave_remainder ? 1 : 0);
-        if (rem && rem < wave_remainder) lane += (rem + kLaneBlocks - 1) / kLaneBlocks;
-    }
-    const size_t lane_tiles = (lane + kLanesPerTile - 1) / kLanesPerTile;
-    *tiles = wave + lane_tiles;
-    *slots = wave + lane_tiles * kLanesPerTile;
-}
-
-int launch_plan(tdes_ctx *c, const void *sched, uint8_t *base, bool use_graph, hipStream_t stream) {
-    const uint32_t grid = (uint32_t)c->cu_count * c->groups_per_cu;
-    const tdes::PlanHeader *hdr = reinterpret_cast<const tdes::PlanHeader *>(c->d_plan);
-    const uint32_t *tiles = reinterpret_cast<const uint32_t *>(c->d_plan + 256);
-    const tdes::Slot *slots = reinterpret_cast<const tdes::Slot *>(c->d_plan + slots_offset(c->cap_tiles));
-    const uint32_t *ks = static_cast<const uint32_t *>(sched);
-    if (!use_graph) {
-        if (tdes::launch_batch(ks, hdr, tiles, slots, c->d_counter, base, grid, c->threads, c->tiles_per_draw,
-                               c->capped, stream) != hipSuccess)
-            return TDES_ERR_HIP;
-    } else {
-        if (!c->exec || c->g_sched != sched || c->g_base != base || c->g_tiles != tiles || c->g_slots != slots ||
-            c->g_grid != grid || c->g_threads != c->threads || c->g_draw != c->tiles_per_draw ||
-            c->g_capped != c->capped) {
-            if (c->exec) {
-                (void)hipGraphExecDestroy(c->exec);
-                c->exec = nullptr;
-            }
-            hipGraph_t graph = nullptr;
-            if (hipStreamBeginCapture(c->capture_stream, hipStreamCaptureModeThreadLocal) != hipSuccess)
-                return TDES_ERR_HIP;
-            const hipError_t le = tdes::launch_batch(ks, hdr, tiles, slots, c->d_counter, base, grid, c->threads,
-                                                     c->tiles_per_draw, c->capped, c->capture_stream);
-            const hipError_t ce = hipStreamEndCapture(c->capture_stream, &graph);
-            if (le != hipSuccess || ce != hipSuccess || !graph) {
-                if (graph) (void)hipGraphDestroy(graph);
-                return TDES_ERR_HIP;
-            }
-            const hipError_t ie = hipGraphInstantiate(&c->exec, graph, nullptr, nullptr, 0);
-            (void)hipGraphDestroy(graph);
-            if (ie != hipSuccess) {
-                c->exec = nullptr;
-                return TDES_ERR_HIP;
-            }
-            c->g_sched = sched;
-            c->g_base = base;
-            c->g_tiles = tiles;
-            c->g_slots = slots;
-            c->g_grid = grid;
-            c->g_threads = c->threads;
-            c->g_draw = c->tiles_per_draw;
-            c->g_capped = c->capped;
-            c->info.graph_captures++;
-        }
-        if (hipGraphLaunch(c->exec, stream) != hipSuccess) return TDES_ERR_HIP;
-    }
-    if (hipEventRecord(c->plan_done, stream) != hipSuccess) return TDES_ERR_HIP;
+    *plan = p;
     return TDES_OK;
+}
+
+// The planned batch's kernel: a workgroup per tile for few tiles, one wave per tile for many.
+hipError_t launch_kernel(tdes_ctx *c, const void *sched, uint8_t *base, hipStream_t stream) {
+    const tdes::PlanHeader *hdr = reinterpret_cast<const tdes::PlanHeader *>(c->d_plan);
+    const tdes::Slot *slots = reinterpret_cast<const tdes::Slot *>(c->d_plan + sizeof(tdes::PlanHeader));
+    const uint32_t *ks = static_cast<const uint32_t *>(sched);
+    if (c->last_tiles <= tdes::kTeamTiles) return tdes::launch_batch_team(ks, hdr, slots, base, stream);
+    return tdes::launch_batch(ks, hdr, slots, c->d_counter, base, (uint32_t)c->cu_count * c->groups_per_cu, c->threads,
+                              c->tiles_per_draw, c->capped, stream);
+}
+
+// The graph of that launch, captured if the context has none for it; nullptr on failure.
+hipGraphExec_t plan_graph(tdes_ctx *c, const void *sched, uint8_t *base) {
+    const bool team = c->last_tiles <= tdes::kTeamTiles;
+    const uint32_t grid = (uint32_t)c->cu_count * c->groups_per_cu;
+    tdes_ctx::Graph &g = c->graphs[team];
+    const bool same_shape = team || (g.grid == grid && g.threads == c->threads && g.draw == c->tiles_per_draw &&
+                                     g.capped == c->capped);
+    if (g.exec && g.sched == sched && g.base == base && g.plan == c->d_plan && same_shape) return g.exec;
+    g.drop();
+    hipGraph_t graph = nullptr;
+    if (hipStreamBeginCapture(c->capture_stream, hipStreamCaptureModeThreadLocal) != hipSuccess) return nullptr;
+    const hipError_t le = launch_kernel(c, sched, base, c->capture_stream);
+    const hipError_t ce = hipStreamEndCapture(c->capture_stream, &graph);
+    if (le != hipSuccess || ce != hipSuccess || !graph) {
+        if (graph) (void)hipGraphDestroy(graph);
+        return nullptr;
+    }
+    const hipError_t ie = hipGraphInstantiate(&g.exec, graph, nullptr, nullptr, 0);
+    (void)hipGraphDestroy(graph);
+    if (ie != hipSuccess) {
+        g.exec = nullptr;
+        return nullptr;
+    }
+    g.sched = sched;
+    g.base = base;
+    g.plan = c->d_plan;
+    g.grid = grid;
+    g.threads = c->threads;
+    g.draw = c->tiles_per_draw;
+    g.capped = c->capped;
+    c->info.graph_captures++;
+    return g.exec;
 }
 
 }  // namespace
@@ -305,7 +286,7 @@ extern "C" int tdes_ctx_destroy(tdes_ctx *c) {
     tdes::DeviceGuard guard(c->device);
     if (c->plan_done) (void)hipEventSynchronize(c->plan_done);
     if (c->staging_free) (void)hipEventSynchronize(c->staging_free);
-    if (c->exec) (void)hipGraphExecDestroy(c->exec);
+    for (auto &g : c->graphs) g.drop();
     if (c->d_plan) (void)hipFree(c->d_plan);
     if (c->h_plan) (void)hipHostFree(c->h_plan);
     if (c->d_counter) (void)hipFree(c->d_counter);
@@ -371,29 +352,39 @@ extern "C" int tdes_ecb_batch(tdes_ctx *c, const tdes_job *jobs, uint32_t n_jobs
         return TDES_OK;
     }
 
-    size_t max_tiles, max_slots;
-    count_bounds(jobs, n_jobs, c->wave_remainder, &max_tiles, &max_slots);
-    if (max_tiles >= (size_t)tdes::kLaneTileBit || max_slots >= (size_t)tdes::kLaneTileBit) return TDES_ERR_SIZE;
-    rc = ensure_capacity(c, max_tiles, max_slots);
+    rc = ensure_records(c, n_jobs);
     if (rc != TDES_OK) return rc;
-    // The staging buffer must not change under a previous upload.
-    if (hipEventSynchronize(c->staging_free) != hipSuccess) return TDES_ERR_HIP;
-    uint32_t n_tiles = 0, n_slots = 0;
-    plan_jobs(c, jobs, n_jobs, &n_tiles, &n_slots, &c->info);
-    // A previous launch on another stream may still read the device plan.
-    if (hipStreamWaitEvent(s, c->plan_done, 0) != hipSuccess) return TDES_ERR_HIP;
-    const size_t so = slots_offset(c->cap_tiles);
-    if (hipMemcpyAsync(c->d_plan, c->h_plan, 256 + (size_t)n_tiles * 4, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(c->d_plan + so, c->h_plan + so, (size_t)n_slots * sizeof(tdes::Slot), hipMemcpyHostToDevice,
-                       s) != hipSuccess ||
-        hipEventRecord(c->staging_free, s) != hipSuccess)
-        return TDES_ERR_HIP;
+    Plan p;
+    rc = plan_jobs(c, jobs, n_jobs, &p);
+    if (rc != TDES_OK) return rc;
+    rc = ensure_slots(c, p.slots());
+    if (rc != TDES_OK) return rc;
+    c->info.tiles = p.tiles();
+    c->info.wave_tiles = p.wave;
+    c->info.lane_tiles = p.lane_tiles();
+    c->info.slots = p.slots();
+    c->info.blocks = p.blocks;
+    c->info.padded_blocks = p.tiles() * kWaveBlocks;
     c->have_plan = true;
     c->last_sched = dev_sched_table;
     c->last_base = base;
-    c->last_tiles = n_tiles;
-    if (n_tiles == 0) return TDES_OK;
-    return launch_plan(c, dev_sched_table, base, !(flags & TDES_BATCH_NO_GRAPH), s);
+    c->last_tiles = (uint32_t)p.tiles();
+    if (p.messages == 0) return TDES_OK;
+    // A previous launch on another stream may still read the device plan.
+    if (hipStreamWaitEvent(s, c->plan_done, 0) != hipSuccess ||
+        tdes::launch_plan(c->h_plan, p.messages, p.max_wave, reinterpret_cast<tdes::PlanHeader *>(c->d_plan),
+                          reinterpret_cast<tdes::Slot *>(c->d_plan + sizeof(tdes::PlanHeader)), (uint32_t)p.tiles(),
+                          (uint32_t)p.lane, s) != hipSuccess ||
+        hipEventRecord(c->staging_free, s) != hipSuccess) {
+        c->have_plan = false;
+        return TDES_ERR_HIP;
+    }
+    // The graph is captured here, for replays.  This launch follows the plan kernel directly: as a graph it
+    // would start 7 us later.
+    if (!(flags & TDES_BATCH_NO_GRAPH) && !plan_graph(c, dev_sched_table, base)) return TDES_ERR_HIP;
+    if (launch_kernel(c, dev_sched_table, base, s) != hipSuccess || hipEventRecord(c->plan_done, s) != hipSuccess)
+        return TDES_ERR_HIP;
+    return TDES_OK;
 }
 
 extern "C" int tdes_ecb_batch_replay(tdes_ctx *c, uint32_t flags, void *stream) {
@@ -404,8 +395,14 @@ extern "C" int tdes_ecb_batch_replay(tdes_ctx *c, uint32_t flags, void *stream) 
     tdes::DeviceGuard guard(c->device);
     if (!guard.ok()) return TDES_ERR_HIP;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // Order after the plan's upload and the previous launch, whichever streams they ran on.
+    // Order after the plan kernel and the previous launch, whichever streams they ran on.
     if (hipStreamWaitEvent(s, c->staging_free, 0) != hipSuccess || hipStreamWaitEvent(s, c->plan_done, 0) != hipSuccess)
         return TDES_ERR_HIP;
-    return launch_plan(c, c->last_sched, c->last_base, !(flags & TDES_BATCH_NO_GRAPH), s);
+    if (flags & TDES_BATCH_NO_GRAPH) {
+        if (launch_kernel(c, c->last_sched, c->last_base, s) != hipSuccess) return TDES_ERR_HIP;
+    } else {
+        hipGraphExec_t exec = plan_graph(c, c->last_sched, c->last_base);
+        if (!exec || hipGraphLaunch(exec, s) != hipSuccess) return TDES_ERR_HIP;
+    }
+    return hipEventRecord(c->plan_done, s) == hipSuccess ? TDES_OK : TDES_ERR_HIP;
 }

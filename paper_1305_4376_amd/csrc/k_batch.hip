@@ -74,11 +74,10 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
 #endif
 
 TDES_BATCH_KERNEL(const uint32_t *__restrict__ sched, const tdes::PlanHeader *__restrict__ hdr,
-                  const uint32_t *__restrict__ tiles, const tdes::Slot *__restrict__ slots, uint32_t *counter,
-                  uint8_t *base, uint32_t per_draw) {
+                  const tdes::Slot *__restrict__ slots, uint32_t *counter, uint8_t *base, uint32_t per_draw) {
     const uint32_t lane = threadIdx.x % kLanes;
     const uint32_t n_tiles = hdr->n_tiles;
-    const uint32_t n_slots = hdr->n_slots;
+    const uint32_t n_lane_tiles = hdr->n_lane_tiles;
     const uint32_t n_waves = gridDim.x * (blockDim.x / kLanes);
     const uint32_t wave_id = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x / kLanes) + threadIdx.x / kLanes);
     if (wave_id >= n_tiles) return;
@@ -89,15 +88,12 @@ TDES_BATCH_KERNEL(const uint32_t *__restrict__ sched, const tdes::PlanHeader *__
     while (first < n_tiles) {
         const uint32_t end = (uint32_t)min((uint64_t)n_tiles, first + count);
         for (uint32_t ticket = (uint32_t)first; ticket < end; ticket++) {
-            const uint32_t t = __builtin_amdgcn_readfirstlane(tiles[ticket]);
-            const uint32_t first_slot = t & ~tdes::kLaneTileBit;
-            if (t & tdes::kLaneTileBit) {
+            const uint32_t first_slot = tdes::tile_slot(ticket, n_lane_tiles);
+            if (ticket < n_lane_tiles) {
                 // Lane tile: 64 slots, one per lane.
-                if (first_slot + kLanes > n_slots) continue;
                 const tdes::Slot s = slots[first_slot + lane];
                 lane_slot(sched + s.ks_off, base + s.in_off, base + s.out_off, s.count);
             } else {
-                if (first_slot >= n_slots) continue;
                 // The slot is the same for the whole wave: keep its fields in scalar registers.
                 const tdes::Slot &sl = slots[first_slot];
                 const uint64_t in_off = uniform64(sl.in_off), out_off = uniform64(sl.out_off);
@@ -122,21 +118,21 @@ TDES_BATCH_KERNEL(const uint32_t *__restrict__ sched, const tdes::PlanHeader *__
 namespace tdes {
 
 #ifdef TDES_BATCH_CAPPED
-hipError_t launch_batch_capped(const uint32_t *sched, const PlanHeader *hdr, const uint32_t *tiles, const Slot *slots,
-                               uint32_t *counter, uint8_t *base, uint32_t grid, uint32_t threads,
-                               uint32_t tiles_per_draw, hipStream_t stream) {
-    hipLaunchKernelGGL(tdes_batch_kernel_capped, dim3(grid), dim3(threads), 0, stream, sched, hdr, tiles, slots,
+hipError_t launch_batch_capped(const uint32_t *sched, const PlanHeader *hdr, const Slot *slots, uint32_t *counter,
+                               uint8_t *base, uint32_t grid, uint32_t threads, uint32_t tiles_per_draw,
+                               hipStream_t stream) {
+    hipLaunchKernelGGL(tdes_batch_kernel_capped, dim3(grid), dim3(threads), 0, stream, sched, hdr, slots,
                        counter, base, tiles_per_draw);
     return hipGetLastError();
 }
 #else
-hipError_t launch_batch(const uint32_t *sched, const PlanHeader *hdr, const uint32_t *tiles, const Slot *slots,
-                        uint32_t *counter, uint8_t *base, uint32_t grid, uint32_t threads, uint32_t tiles_per_draw,
-                        bool capped, hipStream_t stream) {
+hipError_t launch_batch(const uint32_t *sched, const PlanHeader *hdr, const Slot *slots, uint32_t *counter,
+                        uint8_t *base, uint32_t grid, uint32_t threads, uint32_t tiles_per_draw, bool capped,
+                        hipStream_t stream) {
     if (threads == 0 || threads > kMaxThreads || threads % kLanes != 0 || grid == 0 || tiles_per_draw == 0)
         return hipErrorInvalidValue;
-    if (capped) return launch_batch_capped(sched, hdr, tiles, slots, counter, base, grid, threads, tiles_per_draw, stream);
-    hipLaunchKernelGGL(tdes_batch_kernel, dim3(grid), dim3(threads), 0, stream, sched, hdr, tiles, slots, counter,
+    if (capped) return launch_batch_capped(sched, hdr, slots, counter, base, grid, threads, tiles_per_draw, stream);
+    hipLaunchKernelGGL(tdes_batch_kernel, dim3(grid), dim3(threads), 0, stream, sched, hdr, slots, counter,
                        base, tiles_per_draw);
     return hipGetLastError();
 }
