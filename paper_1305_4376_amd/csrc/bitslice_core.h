@@ -330,6 +330,14 @@ enum class TileMode { kEcb, kCtr, kCbcDecrypt };
 __device__ __forceinline__ uint32_t be_hi_word(uint64_t v) { return __builtin_bswap32((uint32_t)(v >> 32)); }
 __device__ __forceinline__ uint32_t be_lo_word(uint64_t v) { return __builtin_bswap32((uint32_t)v); }
 
+// Blocks of the tile that starts `left` (wave-uniform, below 2^43) blocks before a message's end.  The 32-bit
+// comparison is deliberate: of the 64-bit minimum of a uniform value and a constant, hipcc (ROCm 7.2) has
+// selected by a condition bit that other instructions had overwritten.
+__device__ __forceinline__ uint32_t tile_count(uint64_t left) {
+    const uint32_t whole = __builtin_amdgcn_readfirstlane((uint32_t)(left / kTileBlocks));
+    return whole ? kTileBlocks : __builtin_amdgcn_readfirstlane((uint32_t)left);
+}
+
 // A wave tile: 2048 consecutive blocks starting at `tin`/`tout` (wave-uniform),
 // blocks first_block.. of the message; lane l holds blocks 128k + 2l and
 // 128k + 2l + 1 (k = 0..15), so each access is 16 bytes per lane over 1 KiB

@@ -21,9 +21,7 @@ __global__ __launch_bounds__(kTeamThreads) void tdes_team_kernel(const uint32_t 
                                                                  uint8_t *out, uint64_t n_blocks, uint64_t iv) {
     __shared__ uint32_t lds[kTeamWords];
     const uint64_t first = (uint64_t)blockIdx.x * kTileBlocks;
-    const uint64_t left = n_blocks - first;
-    const uint32_t n_valid = left < kTileBlocks ? (uint32_t)left : kTileBlocks;
-    team_tile<kMode, false>(ks, in + 8 * first, out + 8 * first, n_valid, threadIdx.x, first, iv, lds);
+    team_tile<kMode, false>(ks, in + 8 * first, out + 8 * first, tile_count(n_blocks - first), threadIdx.x, first, iv, lds);
 }
 
 template <TileMode kMode>
