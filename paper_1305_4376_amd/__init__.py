@@ -145,6 +145,21 @@ def _ptr(x) -> int | None:
     raise TypeError(f"cannot take the address of {type(x).__name__}")
 
 
+_torch_fast = None
+
+
+def _torch():
+    """(torch.Tensor, a function from a device index to the handle of its current stream)."""
+    global _torch_fast
+    if _torch_fast is None:
+        import torch
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is None:
+            raw = lambda index: torch.cuda.current_stream(index).cuda_stream  # noqa: E731
+        _torch_fast = (torch.Tensor, raw)
+    return _torch_fast
+
+
 def _stream(stream, like=None):
     if stream is not None:
         return stream if isinstance(stream, int) else stream.cuda_stream
@@ -189,13 +204,23 @@ def _nblocks(buf, n_blocks):
     raise ValueError("n_blocks is required for raw addresses")
 
 
-def _message_args(dev_sched, src, dst, n_blocks):
-    """Block count of a one-message call, with every sized buffer checked against it."""
+def _message_args(dev_sched, src, dst, n_blocks, stream=None):
+    """(schedule, input, output, block count, stream) of a one-message call as the C entry takes them,
+    with every sized buffer checked against the call."""
+    if n_blocks is None and stream is None:
+        # The ordinary call, tensors without a count or a stream.  Its host time is most of a short
+        # message's, so each fact is asked of torch once, and anything unusual goes the general way.
+        tensor, raw_stream = _torch()
+        if type(src) is tensor and type(dst) is tensor and type(dev_sched) is tensor:
+            index, have = src.get_device(), src.nbytes
+            if (index >= 0 and not have % 8 and dst.nbytes >= have and dev_sched.nbytes >= TDES_SCHED_BYTES
+                    and src.is_contiguous() and dst.is_contiguous() and dev_sched.is_contiguous()):
+                return dev_sched.data_ptr(), src.data_ptr(), dst.data_ptr(), have // 8, raw_stream(index)
     n = _nblocks(src, n_blocks)
     _need(dev_sched, TDES_SCHED_BYTES, "schedule")
     _need(src, 8 * n, "input")
     _need(dst, 8 * n, "output")
-    return n
+    return _ptr(dev_sched), _ptr(src), _ptr(dst), n, _stream(stream, src)
 
 
 def _check(rc: int, where: str):
@@ -236,51 +261,43 @@ def tdes_sched_upload(host, dev_table, count: int | None = None, stream=None) ->
 
 def tdes_ecb_run(dev_sched, src, dst, n_blocks=None, direction: int = TDES_ENCRYPT,
                  variant: int = TDES_VARIANT_AUTO, stream=None) -> None:
-    n = _message_args(dev_sched, src, dst, n_blocks)
-    _check(load_library().tdes_ecb_run(_ptr(dev_sched), _ptr(src), _ptr(dst), n, int(direction), int(variant),
-                                       _stream(stream, src)), "tdes_ecb_run")
+    sched, a, b, n, s = _message_args(dev_sched, src, dst, n_blocks, stream)
+    _check(load_library().tdes_ecb_run(sched, a, b, n, int(direction), int(variant), s), "tdes_ecb_run")
 
 
 def _iv_buffer(iv):
     b = bytes(iv) if iv is not None else None
     if b is not None and len(b) != 8:
         raise ValueError("an IV is 8 bytes")
-    return ctypes.create_string_buffer(b, 8) if b is not None else None
+    return b
 
 
 def tdes_ecb_chunked(dev_sched, src, dst, chunk_blocks: int, n_blocks=None, direction: int = TDES_ENCRYPT,
                      variant: int = TDES_VARIANT_AUTO, threads: int = 0, stream=None) -> None:
     """The paper's host loop: one launch per chunk of chunk_blocks blocks, workgroups of `threads` (0: default)."""
-    n = _message_args(dev_sched, src, dst, n_blocks)
-    _check(load_library().tdes_ecb_chunked(_ptr(dev_sched), _ptr(src), _ptr(dst), n, int(chunk_blocks),
-                                           int(direction), int(variant), int(threads), _stream(stream, src)),
-           "tdes_ecb_chunked")
+    sched, a, b, n, s = _message_args(dev_sched, src, dst, n_blocks, stream)
+    _check(load_library().tdes_ecb_chunked(sched, a, b, n, int(chunk_blocks), int(direction), int(variant),
+                                           int(threads), s), "tdes_ecb_chunked")
 
 
 def tdes_ctr_crypt(dev_sched, iv, src, dst, n_blocks=None, stream=None) -> None:
     """CTR mode (encrypt or decrypt): dst = src XOR EDE(iv + j)."""
-    n = _message_args(dev_sched, src, dst, n_blocks)
-    _check(load_library().tdes_ctr_crypt(_ptr(dev_sched), _iv_buffer(iv), _ptr(src), _ptr(dst), n,
-                                         _stream(stream, src)), "tdes_ctr_crypt")
+    sched, a, b, n, s = _message_args(dev_sched, src, dst, n_blocks, stream)
+    _check(load_library().tdes_ctr_crypt(sched, _iv_buffer(iv), a, b, n, s), "tdes_ctr_crypt")
 
 
 def tdes_cbc_decrypt(dev_sched, iv, src, dst, n_blocks=None, stream=None) -> None:
     """CBC decryption: dst[j] = EDE^-1(src[j]) XOR src[j-1], src[-1] = iv; src and dst must not overlap."""
-    n = _message_args(dev_sched, src, dst, n_blocks)
-    _check(load_library().tdes_cbc_decrypt(_ptr(dev_sched), _iv_buffer(iv), _ptr(src), _ptr(dst), n,
-                                           _stream(stream, src)), "tdes_cbc_decrypt")
+    sched, a, b, n, s = _message_args(dev_sched, src, dst, n_blocks, stream)
+    _check(load_library().tdes_cbc_decrypt(sched, _iv_buffer(iv), a, b, n, s), "tdes_cbc_decrypt")
 
 
 def tdes_ecb_encrypt(dev_sched, src, dst, n_blocks=None, stream=None) -> None:
-    n = _message_args(dev_sched, src, dst, n_blocks)
-    _check(load_library().tdes_ecb_encrypt(_ptr(dev_sched), _ptr(src), _ptr(dst), n, _stream(stream, src)),
-           "tdes_ecb_encrypt")
+    _check((_lib or load_library()).tdes_ecb_encrypt(*_message_args(dev_sched, src, dst, n_blocks, stream)), "tdes_ecb_encrypt")
 
 
 def tdes_ecb_decrypt(dev_sched, src, dst, n_blocks=None, stream=None) -> None:
-    n = _message_args(dev_sched, src, dst, n_blocks)
-    _check(load_library().tdes_ecb_decrypt(_ptr(dev_sched), _ptr(src), _ptr(dst), n, _stream(stream, src)),
-           "tdes_ecb_decrypt")
+    _check((_lib or load_library()).tdes_ecb_decrypt(*_message_args(dev_sched, src, dst, n_blocks, stream)), "tdes_ecb_decrypt")
 
 
 def tdes_fill_splitmix64(dev, n_words: int, seed: int, first: int = 0, stream=None) -> None:
@@ -429,6 +446,9 @@ def tdes_server_run_trace(server: int, reqs: np.ndarray, arrival_s: np.ndarray) 
 def tdes_ecb_host(dev_sched, host_in, host_out, n_blocks=None, direction: int = TDES_ENCRYPT,
                   chunk_blocks: int = 1 << 22, stream=None) -> None:
     """ECB over a host-resident message (numpy arrays or pinned tensors), copies overlapped in chunks."""
-    n = _message_args(dev_sched, host_in, host_out, n_blocks)
+    n = _nblocks(host_in, n_blocks)
+    _need(dev_sched, TDES_SCHED_BYTES, "schedule")
+    _need(host_in, 8 * n, "input")
+    _need(host_out, 8 * n, "output")
     _check(load_library().tdes_ecb_host(_ptr(dev_sched), _ptr(host_in), _ptr(host_out), int(n), int(direction),
                                         int(chunk_blocks), _stream(stream)), "tdes_ecb_host")
