@@ -109,8 +109,9 @@ int tdes_ecb_decrypt(const void *dev_sched, const void *in, void *out, uint64_t 
 /*
  * Kernel variants.  TDES_VARIANT_AUTO is the shipped default: the fastest
  * kernel on MI355X for the message's size.  Short messages take one bit of the
- * round function per lane, then come the table kernel, a workgroup per tile of
- * 2048 blocks, and from about 2^21 blocks on the bitsliced kernel.
+ * round function per lane, then come table lookups with two lanes or one per
+ * block, a workgroup per tile of 2048 blocks, and from about 2^21 blocks on the
+ * bitsliced kernel.
  */
 #define TDES_VARIANT_AUTO 0
 #define TDES_VARIANT_TABLE 1    /* combined S-box/P tables in LDS, one block per lane */

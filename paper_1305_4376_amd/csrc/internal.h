@@ -67,17 +67,26 @@ hipError_t launch_team_ctr(const uint32_t *ks, const uint8_t *in, uint8_t *out, 
                            hipStream_t stream);
 hipError_t launch_team_cbc_decrypt(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, uint64_t iv,
                                    hipStream_t stream);
+// Shortish messages (k_pair.hip): table lookups, two lanes per block.  n_blocks below 2^31.
+hipError_t launch_pair_ecb(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, hipStream_t stream);
+hipError_t launch_pair_ctr(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, uint64_t iv,
+                           hipStream_t stream);
+hipError_t launch_pair_cbc_decrypt(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, uint64_t iv,
+                                   hipStream_t stream);
 // TDES_VARIANT_AUTO by message length, from launches back to back on MI355X:
-//   below kShortBelow      one bit of f per lane: 3.0 us to 2048 blocks, 4.4 at 8192, then 0.29 us per 1024;
-//                          meets the table kernel's 6.2 us at about 14500;
-//   below kAutoTableBelow  the table kernel: 6.2 us to 2^16 blocks, 6.7 at 2^17, 9.9 at 2^18, 16.2 at 3 * 2^17,
-//                          where the team takes 15.0 (14.8 from the shortest message on);
-//   below kTeamBelow       a team per tile: 30.6 us at 2^21 and 43 at 3 * 2^20, one wave per tile 35.1 and 39.2;
-//   from there on          one wave per tile.
-// The modes have no table kernel: one bit per lane meets the team's 14.8 us at about 46000 blocks.
-constexpr uint64_t kShortBelow = 14336;
-constexpr uint64_t kShortModesBelow = 45056;
-constexpr uint64_t kAutoTableBelow = 5ull << 16;
+//   below kShortBelow   one bit of f per lane: 3.0 us to 2048 blocks, 4.4 at 8192, then 0.29 us per 1024;
+//   to kPairTo          two lanes per block: 5.3 us at 8192, 5.7 at 65536, 6.8 at 98304;
+//   to kTableTo         the table kernel: 6.4 us at 65536, 6.6 at 2^17, 9.8 at 2^18, where each lane has one
+//                       block (with a second pass 16.1 from there on);
+//   to kPairAgainTo     two lanes per block: 13.2 us at 5 * 2^16, 14.7 at 3 * 2^17;
+//   below kTeamBelow    a team per tile: 14.8 us from the shortest message to 3 * 2^17, 30.6 at 2^21, 43 at
+//                       3 * 2^20, where one wave per tile takes 39 (35.1 at 2^21);
+//   from there on       one wave per tile.
+// The modes have no one-lane table kernel: two lanes per block from kShortBelow to kPairAgainTo.
+constexpr uint64_t kShortBelow = 12288;
+constexpr uint64_t kPairTo = 90112;
+constexpr uint64_t kTableTo = 1ull << 18;
+constexpr uint64_t kPairAgainTo = 3ull << 17;
 constexpr uint64_t kTeamBelow = 9ull << 18;
 hipError_t launch_auto(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, hipStream_t stream);
 // Block-parallel modes (bitsliced): ks is the encryption half for CTR and the

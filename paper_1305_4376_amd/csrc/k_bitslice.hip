@@ -100,14 +100,16 @@ hipError_t launch_bitslice(const uint32_t *ks, const uint8_t *in, uint8_t *out, 
 
 hipError_t launch_ctr(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, uint64_t iv,
                       hipStream_t stream) {
-    if (n_blocks < kShortModesBelow) return launch_short_ctr(ks, in, out, n_blocks, iv, stream);
+    if (n_blocks < kShortBelow) return launch_short_ctr(ks, in, out, n_blocks, iv, stream);
+    if (n_blocks <= kPairAgainTo) return launch_pair_ctr(ks, in, out, n_blocks, iv, stream);
     if (n_blocks < kTeamBelow) return launch_team_ctr(ks, in, out, n_blocks, iv, stream);
     return launch<TileMode::kCtr>(ks, in, out, n_blocks, iv, stream);
 }
 
 hipError_t launch_cbc_decrypt(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, uint64_t iv,
                               hipStream_t stream) {
-    if (n_blocks < kShortModesBelow) return launch_short_cbc_decrypt(ks, in, out, n_blocks, 0, iv, stream);
+    if (n_blocks < kShortBelow) return launch_short_cbc_decrypt(ks, in, out, n_blocks, 0, iv, stream);
+    if (n_blocks <= kPairAgainTo) return launch_pair_cbc_decrypt(ks, in, out, n_blocks, iv, stream);
     if (n_blocks < kTeamBelow) return launch_team_cbc_decrypt(ks, in, out, n_blocks, iv, stream);
     return launch<TileMode::kCbcDecrypt>(ks, in, out, n_blocks, iv, stream);
 }
