@@ -305,8 +305,8 @@ int tdes_ctx_get_info(const tdes_ctx *ctx, tdes_batch_info *info);
  *             bytes without being equal.  A refused job's output is not
  *             written.  If the call's wave tiles (2048 blocks each, per job
  *             rounded up) total 2^31 or more, every job is refused.
- * Runs on the current device, on `stream` (which must belong to it): a plan
- * launch, then the cipher launch.  Every call on one GPU uses that GPU's one
+ * Runs on the current device, on `stream` (which must belong to it): one launch
+ * for few jobs in a small buffer, else a plan launch and the cipher's.  Every call on one GPU uses that GPU's one
  * array, so calls whose launches may overlap on the same GPU race: order
  * them (one stream, or events).  As with tdes_ecb_batch, no message may
  * write bytes another message of the call reads or writes (not checked here).

@@ -52,12 +52,16 @@ struct tdes_ctx {
     int cu_count = 0;
     hipStream_t capture_stream = nullptr;
     uint32_t *d_counter = nullptr;
-    // The plan: the messages' records in pinned host memory, the header and slots on the device.
+    // The plan: the messages' records in pinned host memory, in two buffers in turn so that the host writes one
+    // batch's while the GPU works on the last; the header and slots on the device.
     uint8_t *d_plan = nullptr;
-    tdes::PlanMessage *h_plan = nullptr;
-    size_t cap_slots = 0, cap_messages = 0;
-    hipEvent_t staging_free = nullptr;  // the last plan kernel has read the records
-    hipEvent_t plan_done = nullptr;     // the last kernel has finished with the device plan
+    size_t cap_slots = 0;
+    struct Records {
+        tdes::PlanMessage *host = nullptr;
+        size_t cap = 0;
+        hipEvent_t done = nullptr;  // the batch with these records, and its last replay, have finished
+    } records[2];
+    int last = 0;  // the last batch's records
     bool have_plan = false;
     // Last planned batch (for replay).
     const void *last_sched = nullptr;
@@ -86,20 +90,19 @@ struct tdes_ctx {
 
 namespace {
 
-// Room for n_messages records; the last plan kernel has read the old ones on return.
-int ensure_records(tdes_ctx *c, size_t n_messages) {
-    // The records must not change under a previous plan kernel.
-    if (hipEventSynchronize(c->staging_free) != hipSuccess) return TDES_ERR_HIP;
-    if (n_messages <= c->cap_messages) return TDES_OK;
-    const size_t n = std::max<size_t>(n_messages, std::max<size_t>(1024, c->cap_messages * 2));
-    if (c->h_plan) (void)hipHostFree(c->h_plan);
-    c->h_plan = nullptr;
-    c->cap_messages = 0;
-    if (hipHostMalloc(&c->h_plan, n * sizeof(tdes::PlanMessage), hipHostMallocDefault) != hipSuccess) {
-        c->h_plan = nullptr;
+// Room for n_messages records, no longer read by an earlier batch's plan kernel.
+int ensure_records(tdes_ctx::Records *r, size_t n_messages) {
+    if (hipEventSynchronize(r->done) != hipSuccess) return TDES_ERR_HIP;
+    if (n_messages <= r->cap) return TDES_OK;
+    const size_t n = std::max<size_t>(n_messages, std::max<size_t>(1024, r->cap * 2));
+    if (r->host) (void)hipHostFree(r->host);
+    r->host = nullptr;
+    r->cap = 0;
+    if (hipHostMalloc(&r->host, n * sizeof(tdes::PlanMessage), hipHostMallocDefault) != hipSuccess) {
+        r->host = nullptr;
         return TDES_ERR_NOMEM;
     }
-    c->cap_messages = n;
+    r->cap = n;
     return TDES_OK;
 }
 
@@ -109,7 +112,7 @@ int ensure_slots(tdes_ctx *c, size_t n_slots) {
     const size_t n = std::max<size_t>(n_slots, std::max<size_t>(8192, c->cap_slots * 2));
     if (c->d_plan) {
         // The old buffer may still be in use by a kernel, and the captured graphs point into it.
-        if (hipEventSynchronize(c->plan_done) != hipSuccess) return TDES_ERR_HIP;
+        if (hipEventSynchronize(c->records[c->last].done) != hipSuccess) return TDES_ERR_HIP;
         for (auto &g : c->graphs) g.drop();
         (void)hipFree(c->d_plan);
         c->d_plan = nullptr;
@@ -190,15 +193,15 @@ struct Plan {
 };
 
 // Writes the records of a batch (there is room for n_jobs).  TDES_ERR_SIZE if it has too many slots.
-int plan_jobs(tdes_ctx *c, const tdes_job *jobs, uint32_t n_jobs, Plan *plan) {
+int plan_jobs(uint32_t wave_remainder, const tdes_job *jobs, uint32_t n_jobs, tdes::PlanMessage *records, Plan *plan) {
     Plan p;
     for (uint32_t j = 0; j < n_jobs; j++) {
         const tdes_job &x = jobs[j];
         if (x.n_blocks == 0) continue;
         const uint32_t rem = (uint32_t)(x.n_blocks % kWaveBlocks);
-        const bool wave_rem = rem >= c->wave_remainder;
+        const bool wave_rem = rem >= wave_remainder;
         const uint64_t wave = x.n_blocks / kWaveBlocks + wave_rem;
-        tdes::PlanMessage &m = c->h_plan[p.messages++];
+        tdes::PlanMessage &m = records[p.messages++];
         m.in_off = x.in_off;
         m.out_off = x.out_off;
         m.n_blocks = x.n_blocks;
@@ -217,11 +220,13 @@ int plan_jobs(tdes_ctx *c, const tdes_job *jobs, uint32_t n_jobs, Plan *plan) {
 }
 
 // The planned batch's kernel: a workgroup per tile for few tiles, one wave per tile for many.
-hipError_t launch_kernel(tdes_ctx *c, const void *sched, uint8_t *base, hipStream_t stream) {
+// captured: the launch is replayed for other batches of its kind too.
+hipError_t launch_kernel(tdes_ctx *c, const void *sched, uint8_t *base, bool captured, hipStream_t stream) {
     const tdes::PlanHeader *hdr = reinterpret_cast<const tdes::PlanHeader *>(c->d_plan);
     const tdes::Slot *slots = reinterpret_cast<const tdes::Slot *>(c->d_plan + sizeof(tdes::PlanHeader));
     const uint32_t *ks = static_cast<const uint32_t *>(sched);
-    if (c->last_tiles <= tdes::kTeamTiles) return tdes::launch_batch_team(ks, hdr, slots, base, stream);
+    if (c->last_tiles <= tdes::kTeamTiles)
+        return tdes::launch_batch_team(ks, hdr, slots, base, captured ? tdes::kTeamTiles : c->last_tiles, stream);
     return tdes::launch_batch(ks, hdr, slots, c->d_counter, base, (uint32_t)c->cu_count * c->groups_per_cu, c->threads,
                               c->tiles_per_draw, c->capped, stream);
 }
@@ -237,7 +242,7 @@ hipGraphExec_t plan_graph(tdes_ctx *c, const void *sched, uint8_t *base) {
     g.drop();
     hipGraph_t graph = nullptr;
     if (hipStreamBeginCapture(c->capture_stream, hipStreamCaptureModeThreadLocal) != hipSuccess) return nullptr;
-    const hipError_t le = launch_kernel(c, sched, base, c->capture_stream);
+    const hipError_t le = launch_kernel(c, sched, base, true, c->capture_stream);
     const hipError_t ce = hipStreamEndCapture(c->capture_stream, &graph);
     if (le != hipSuccess || ce != hipSuccess || !graph) {
         if (graph) (void)hipGraphDestroy(graph);
@@ -278,8 +283,8 @@ extern "C" int tdes_ctx_create(tdes_ctx **out, int device) {
     c->device = dinfo.device;
     c->cu_count = dinfo.cu_count;
     bool ok = hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking) == hipSuccess &&
-              hipEventCreateWithFlags(&c->staging_free, hipEventDisableTiming) == hipSuccess &&
-              hipEventCreateWithFlags(&c->plan_done, hipEventDisableTiming) == hipSuccess &&
+              hipEventCreateWithFlags(&c->records[0].done, hipEventDisableTiming) == hipSuccess &&
+              hipEventCreateWithFlags(&c->records[1].done, hipEventDisableTiming) == hipSuccess &&
               hipMalloc(&c->d_counter, 256) == hipSuccess && hipMemset(c->d_counter, 0, 256) == hipSuccess &&
               hipDeviceSynchronize() == hipSuccess;
     if (!ok) {
@@ -297,14 +302,15 @@ extern "C" int tdes_ctx_create(tdes_ctx **out, int device) {
 extern "C" int tdes_ctx_destroy(tdes_ctx *c) {
     if (!c) return TDES_OK;
     tdes::DeviceGuard guard(c->device);
-    if (c->plan_done) (void)hipEventSynchronize(c->plan_done);
-    if (c->staging_free) (void)hipEventSynchronize(c->staging_free);
+    for (auto &r : c->records)
+        if (r.done) (void)hipEventSynchronize(r.done);
     for (auto &g : c->graphs) g.drop();
     if (c->d_plan) (void)hipFree(c->d_plan);
-    if (c->h_plan) (void)hipHostFree(c->h_plan);
+    for (auto &r : c->records) {
+        if (r.host) (void)hipHostFree(r.host);
+        if (r.done) (void)hipEventDestroy(r.done);
+    }
     if (c->d_counter) (void)hipFree(c->d_counter);
-    if (c->staging_free) (void)hipEventDestroy(c->staging_free);
-    if (c->plan_done) (void)hipEventDestroy(c->plan_done);
     if (c->capture_stream) (void)hipStreamDestroy(c->capture_stream);
     delete c;
     return TDES_OK;
@@ -365,10 +371,11 @@ extern "C" int tdes_ecb_batch(tdes_ctx *c, const tdes_job *jobs, uint32_t n_jobs
         return TDES_OK;
     }
 
-    rc = ensure_records(c, n_jobs);
+    tdes_ctx::Records &rec = c->records[c->last ^ 1];
+    rc = ensure_records(&rec, n_jobs);
     if (rc != TDES_OK) return rc;
     Plan p;
-    rc = plan_jobs(c, jobs, n_jobs, &p);
+    rc = plan_jobs(c->wave_remainder, jobs, n_jobs, rec.host, &p);
     if (rc != TDES_OK) return rc;
     rc = ensure_slots(c, p.slots());
     if (rc != TDES_OK) return rc;
@@ -383,21 +390,22 @@ extern "C" int tdes_ecb_batch(tdes_ctx *c, const tdes_job *jobs, uint32_t n_jobs
     c->last_base = base;
     c->last_tiles = (uint32_t)p.tiles();
     if (p.messages == 0) return TDES_OK;
-    // A previous launch on another stream may still read the device plan.
-    if (hipStreamWaitEvent(s, c->plan_done, 0) != hipSuccess ||
-        tdes::launch_plan(c->h_plan, p.messages, p.max_wave, reinterpret_cast<tdes::PlanHeader *>(c->d_plan),
-                          reinterpret_cast<tdes::Slot *>(c->d_plan + sizeof(tdes::PlanHeader)), (uint32_t)p.tiles(),
-                          (uint32_t)p.lane, s) != hipSuccess ||
-        hipEventRecord(c->staging_free, s) != hipSuccess) {
-        c->have_plan = false;
-        return TDES_ERR_HIP;
-    }
     // The graph is captured here, for replays.  This launch follows the plan kernel directly: as a graph it
-    // would start 7 us later.
-    if (!(flags & TDES_BATCH_NO_GRAPH) && !plan_graph(c, dev_sched_table, base)) return TDES_ERR_HIP;
-    if (launch_kernel(c, dev_sched_table, base, s) != hipSuccess || hipEventRecord(c->plan_done, s) != hipSuccess)
-        return TDES_ERR_HIP;
-    return TDES_OK;
+    // would start 7 us later, and with an event recorded between the two kernels 3 us later.
+    if (!(flags & TDES_BATCH_NO_GRAPH) && !plan_graph(c, dev_sched_table, base)) rc = TDES_ERR_HIP;
+    // A previous launch on another stream may still read the device plan.
+    if (rc == TDES_OK && hipStreamWaitEvent(s, c->records[c->last].done, 0) != hipSuccess) rc = TDES_ERR_HIP;
+    if (rc == TDES_OK) {
+        if (tdes::launch_plan(rec.host, p.messages, p.max_wave, reinterpret_cast<tdes::PlanHeader *>(c->d_plan),
+                              reinterpret_cast<tdes::Slot *>(c->d_plan + sizeof(tdes::PlanHeader)), (uint32_t)p.tiles(),
+                              (uint32_t)p.lane, s) != hipSuccess ||
+            launch_kernel(c, dev_sched_table, base, false, s) != hipSuccess)
+            rc = TDES_ERR_HIP;
+        if (hipEventRecord(rec.done, s) != hipSuccess) rc = TDES_ERR_HIP;
+        c->last ^= 1;
+    }
+    if (rc != TDES_OK) c->have_plan = false;
+    return rc;
 }
 
 extern "C" int tdes_ecb_batch_replay(tdes_ctx *c, uint32_t flags, void *stream) {
@@ -408,14 +416,14 @@ extern "C" int tdes_ecb_batch_replay(tdes_ctx *c, uint32_t flags, void *stream) 
     tdes::DeviceGuard guard(c->device);
     if (!guard.ok()) return TDES_ERR_HIP;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // Order after the plan kernel and the previous launch, whichever streams they ran on.
-    if (hipStreamWaitEvent(s, c->staging_free, 0) != hipSuccess || hipStreamWaitEvent(s, c->plan_done, 0) != hipSuccess)
-        return TDES_ERR_HIP;
+    // Order after the plan kernel and the previous launch, whichever stream they ran on.
+    hipEvent_t done = c->records[c->last].done;
+    if (hipStreamWaitEvent(s, done, 0) != hipSuccess) return TDES_ERR_HIP;
     if (flags & TDES_BATCH_NO_GRAPH) {
-        if (launch_kernel(c, c->last_sched, c->last_base, s) != hipSuccess) return TDES_ERR_HIP;
+        if (launch_kernel(c, c->last_sched, c->last_base, false, s) != hipSuccess) return TDES_ERR_HIP;
     } else {
         hipGraphExec_t exec = plan_graph(c, c->last_sched, c->last_base);
         if (!exec || hipGraphLaunch(exec, s) != hipSuccess) return TDES_ERR_HIP;
     }
-    return hipEventRecord(c->plan_done, s) == hipSuccess ? TDES_OK : TDES_ERR_HIP;
+    return hipEventRecord(done, s) == hipSuccess ? TDES_OK : TDES_ERR_HIP;
 }

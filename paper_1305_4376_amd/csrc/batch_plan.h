@@ -63,6 +63,6 @@ hipError_t launch_batch_capped(const uint32_t *sched, const PlanHeader *hdr, con
 // 1150, a wave per tile 46 and upwards for any batch with lane tiles and 55 for 1466 tiles.
 constexpr uint32_t kTeamTiles = 1152;
 hipError_t launch_batch_team(const uint32_t *sched, const PlanHeader *hdr, const Slot *slots, uint8_t *base,
-                             hipStream_t stream);
+                             uint32_t grid, hipStream_t stream);  // grid: at least the tiles
 
 }  // namespace tdes

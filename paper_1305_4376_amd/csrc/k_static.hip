@@ -8,19 +8,24 @@
 // device array per GPU, `scratch`, whose address is looked up once per device
 // with hipGetSymbolAddress and passed to the kernels from then on.
 //
-// Three launches on the caller's stream:
+// Few jobs in a small buffer (kSmallJobs; the buffer bounds the tiles): one launch.  Every workgroup reads all
+// jobs, counts and sums their tiles in LDS, and takes the tiles of its turn with its eight waves (team_core.h):
+// wave tiles of up to 2048 blocks of one job, and lane tiles of 64 slots of up to 32 blocks, from the jobs'
+// remainders.  512 jobs of up to 8192 blocks (658 tiles by job, 234 packed): 29.8 us a call with the
+// launches below, 22.0 so.
+//
+// Otherwise three launches on the caller's stream:
 //   plan   -- one workgroup reads the jobs, rejects any that is malformed or
 //             reaches outside [dev_base, dev_base + base_bytes) (it gets no
 //             tiles), and writes the exclusive prefix sum of wave tiles (2048
 //             blocks each) per job into scratch, the tile total, the number of
 //             rejected jobs, and a zeroed tile counter;
-//   team   -- if there are at most kTeamTiles tiles, a workgroup per tile (team_core.h);
+//   team   -- if there are at most kTeamTiles tiles, a workgroup per tile;
 //   cipher -- otherwise persistent waves that draw tiles (the first by wave
 //             index, later ones from the counter) and run the bitsliced core on them, with the
 //             job's key masks in scalar registers.
 // Both find each tile's job by binary search over the prefix sums; only the device knows how many tiles
-// there are, so both are launched and one of them ends at once (2 us).  512 jobs of up to 8192 blocks
-// (658 tiles): 46 us a call with the cipher kernel alone, 29.8 with the team.  A job's last tile may be
+// there are, so both are launched and one of them ends at once (4 us).  A job's last tile may be
 // partial: its blocks take the core's per-block path.
 // Nothing here carries state from one call to the next except scratch, which
 // the plan launch rewrites before the cipher launch reads it.
@@ -42,6 +47,9 @@ constexpr uint32_t kPlanThreads = 1024;
 constexpr uint32_t kThreads = 256;
 constexpr uint32_t kGroupsPerCU = 4;
 constexpr uint64_t kMaxJobBlocks = 1ull << 40;
+constexpr uint32_t kSmallJobs = 2 * kTeamThreads;  // two per thread
+constexpr uint32_t kLaneBlocks = 32;
+constexpr uint32_t kWaveRemainder = 1800;          // a remainder of at least this many blocks is a wave tile
 
 // scratch: [header, 256 B][tile_start: kMaxJobs + 1 words]
 struct StaticHeader {
@@ -197,6 +205,92 @@ __global__ __launch_bounds__(kThreads, kGroupsPerCU) void tdes_static_batch_kern
     }
 }
 
+// The whole call by teams, without a plan in memory.  n_jobs <= kSmallJobs, and base_bytes so small that the
+// sums below fit 32 bits.
+__global__ __launch_bounds__(kTeamThreads) void tdes_static_small_kernel(const tdes_job *__restrict__ jobs, uint32_t n_jobs,
+                                                                         const uint32_t *__restrict__ sched,
+                                                                         uint64_t n_scheds, uint8_t *base,
+                                                                         uint64_t base_bytes, uint32_t *dev_rejected) {
+    __shared__ uint32_t lds[kTeamLaneWords];
+    __shared__ uint32_t wave_start[kSmallJobs + 1], lane_start[kSmallJobs + 1];  // exclusive sums over the jobs
+    __shared__ uint32_t part_wave[8], part_lane[8], part_bad[8];
+    const uint32_t tid = threadIdx.x, lane = tid % kLanes, wv = tid / kLanes;
+    uint32_t wave[2], slots[2], bad = 0;
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+        wave[i] = slots[i] = 0;
+        if (2 * tid + i < n_jobs) {
+            const tdes_job x = jobs[2 * tid + i];
+            if (job_ok(x, n_scheds, base_bytes)) {
+                const uint32_t rem = (uint32_t)(x.n_blocks % kTileBlocks), wave_rem = rem >= kWaveRemainder;
+                wave[i] = (uint32_t)(x.n_blocks / kTileBlocks) + wave_rem;
+                if (!wave_rem) slots[i] = (rem + kLaneBlocks - 1) / kLaneBlocks;
+            } else {
+                bad++;
+            }
+        }
+    }
+    // inclusive sums of both counts over the wave's threads, then over the waves
+    uint32_t w = wave[0] + wave[1], s = slots[0] + slots[1];
+#pragma unroll
+    for (int d = 1; d < kLanes; d <<= 1) {
+        const uint32_t pw = __shfl_up(w, d), ps = __shfl_up(s, d);
+        if ((int)lane >= d) { w += pw; s += ps; }
+    }
+#pragma unroll
+    for (int d = 1; d < kLanes; d <<= 1) bad += __shfl_xor(bad, d);
+    if (lane == kLanes - 1) { part_wave[wv] = w; part_lane[wv] = s; part_bad[wv] = bad; }
+    __syncthreads();
+    uint32_t all_wave = 0, all_slots = 0, all_bad = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < 8; i++) {
+        if (i < wv) { w += part_wave[i]; s += part_lane[i]; }
+        all_wave += part_wave[i];
+        all_slots += part_lane[i];
+        all_bad += part_bad[i];
+    }
+    wave_start[2 * tid + 2] = w;
+    wave_start[2 * tid + 1] = w - wave[1];
+    lane_start[2 * tid + 2] = s;
+    lane_start[2 * tid + 1] = s - slots[1];
+    if (tid == 0) {
+        wave_start[0] = lane_start[0] = 0;
+        if (blockIdx.x == 0 && dev_rejected) *dev_rejected = all_bad;
+    }
+    __syncthreads();
+
+    const uint32_t n_lane_tiles = (all_slots + kLanes - 1) / kLanes, n_tiles = n_lane_tiles + all_wave;
+    for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+        if (tile < n_lane_tiles) {
+            // The lane's slot: of the last job that starts at or before it.  Lanes past the end stay idle.
+            const uint32_t slot = tile * kLanes + lane;
+            const uint32_t *ks = sched;
+            const uint8_t *in = base;
+            uint8_t *out = base;
+            uint32_t count = 0;
+            if (slot < all_slots) {
+                uint32_t lo = 0, hi = n_jobs;
+                while (hi - lo > 1) {
+                    const uint32_t mid = (lo + hi) / 2;
+                    if (lane_start[mid] <= slot) lo = mid; else hi = mid;
+                }
+                const tdes_job x = jobs[lo];
+                const uint32_t rem = (uint32_t)(x.n_blocks % kTileBlocks), at = kLaneBlocks * (slot - lane_start[lo]);
+                const uint64_t first = x.n_blocks - rem + at;
+                ks = sched + (uint64_t)x.sched_idx * (TDES_SCHED_BYTES / 4) + x.direction * tdes::kDirWords;
+                in = base + x.in_off + 8 * first;
+                out = base + x.out_off + 8 * first;
+                count = min(kLaneBlocks, rem - at);
+            }
+            team_tile<TileMode::kEcb, true>(ks, in, out, count, tid, 0, 0, lds);
+        } else {
+            const StaticTile t = find_tile(tile - n_lane_tiles, jobs, n_jobs, sched, wave_start, base);
+            team_tile<TileMode::kEcb, false>(t.ks, t.in, t.out, t.count, tid, 0, 0, lds);
+        }
+        __syncthreads();
+    }
+}
+
 // scratch's device address on each GPU, looked up on the first call there.
 constexpr int kMaxDevices = 64;
 std::atomic<uint8_t *> g_scratch[kMaxDevices];
@@ -240,6 +334,16 @@ extern "C" int tdes_ecb_batch_static(const tdes_job *dev_jobs, uint32_t n_jobs, 
     if (tdes::device_info(&info) != TDES_OK) return TDES_ERR_HIP;
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint8_t *base = static_cast<uint8_t *>(dev_base);
+    // Inputs and outputs of different jobs share no bytes, so the buffer bounds the tiles.  (A call that breaks
+    // that rule is still worked off: the workgroups take as many turns as there are tiles.)
+    const uint64_t most_tiles = base_bytes / (8 * kTileBlocks) + n_jobs;
+    if (n_jobs <= kSmallJobs && most_tiles <= tdes::kTeamTiles) {
+        const uint32_t resident = (uint32_t)info.cu_count * 3;  // 48 KiB of LDS per workgroup
+        hipLaunchKernelGGL(tdes_static_small_kernel, dim3(most_tiles < resident ? (uint32_t)most_tiles : resident),
+                           dim3(kTeamThreads), 0, s, dev_jobs, n_jobs, static_cast<const uint32_t *>(dev_sched_table),
+                           n_scheds, base, base_bytes, dev_rejected);
+        return hipGetLastError() == hipSuccess ? TDES_OK : TDES_ERR_HIP;
+    }
     hipLaunchKernelGGL(tdes_static_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, dev_jobs, n_jobs, n_scheds,
                        base_bytes, scr, dev_rejected);
     if (hipGetLastError() != hipSuccess) return TDES_ERR_HIP;

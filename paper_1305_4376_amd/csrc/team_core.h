@@ -34,7 +34,8 @@
 namespace tdes_bs {
 
 constexpr int kTeamThreads = 8 * kLanes;
-constexpr int kTeamWords = 64 * kLanes;  // LDS words
+constexpr int kTeamWords = 64 * kLanes;                // LDS words of a wave tile
+constexpr int kTeamLaneWords = kTeamWords + 96 * kLanes;  // of a lane tile: the lanes' round words behind the planes
 
 // IP output group (of eight bits) that reads bit i (counted from the least significant) of every byte.
 constexpr int ip_row(int i) {
@@ -134,12 +135,12 @@ struct TeamPlanes {
 
 // The three stages by the wave of box S.  lds: this lane's column.  On entry slots 0..31 hold L0 and
 // 32..63 R0, written and not yet waited for; on exit 0..31 hold R16 and 32..63 L16, likewise.  ks: one
-// direction's schedule words, the tile's (wave-uniform) or the lane's (kLaneKeys).
+// direction's schedule words, wave-uniform; with kLaneKeys the lane's column of the round words in LDS.
 template <int S, bool kLaneKeys>
-__device__ __forceinline__ void team_rounds(uint32_t *lds, const uint32_t *__restrict__ ks) {
+__device__ __forceinline__ void team_rounds(uint32_t *lds, const uint32_t *ks) {
     constexpr int kGroup = 4;  // rounds per turn of the loop, and per load of key words
     const uint32_t *fold = ks + kFoldBase;
-    auto word0 = [&](int r) { return kLaneKeys ? ks[2 * r + S % 2] : fold[kFoldOut + r]; };
+    auto word0 = [&](int r) { return kLaneKeys ? ks[kLanes * (2 * r + S % 2)] : fold[kFoldOut + r]; };
     auto word1 = [&](int r) { return kLaneKeys ? 0u : fold[kFoldCorr + r]; };
     TeamPlanes<S, kLaneKeys> a, b;
     uint32_t *x = lds, *y = lds + 32 * kLanes;
@@ -199,16 +200,18 @@ __device__ __forceinline__ void team_rounds(uint32_t *lds, const uint32_t *__res
     a.put(lds + 32 * kLanes);
 }
 
-// A tile by a workgroup of kTeamThreads; every thread of it calls this.  lds: kTeamWords words, free at
-// the call for all waves of the workgroup and free again when the last of them has returned.
+// A tile by a workgroup of kTeamThreads; every thread of it calls this.  lds: kTeamWords words (kTeamLaneWords
+// with a key per lane), free at the call for all waves of the workgroup and free again when the last of them
+// has returned.
 //
 // One key (kLaneKeys false): a wave tile (mode_tile): blocks first_block .. of the message at tin / tout,
 // the first n_valid of the 2048 present; all arguments but tid the same for every thread.
 // A key per lane (ECB): a lane tile (lane_slot): ks, tin, tout and n_valid (up to 32 blocks) are the lane's,
-// the same in every wave.
+// the same in every wave.  The lanes' round words are brought to LDS once: read from memory by the eight waves
+// in every round, 64 lines at a time, they cost as much as the rounds.
 // Blocks that are not present are not loaded and not stored.  8-byte alignment suffices.
 template <TileMode kMode, bool kLaneKeys>
-__device__ __forceinline__ void team_tile(const uint32_t *__restrict__ ks, const uint8_t *tin, uint8_t *tout,
+__device__ __forceinline__ void team_tile(const uint32_t *ks, const uint8_t *tin, uint8_t *tout,
                                           uint32_t n_valid, uint32_t tid, uint64_t first_block, uint64_t iv,
                                           uint32_t *lds) {
     const uint32_t lane = tid % kLanes;
@@ -218,14 +221,38 @@ __device__ __forceinline__ void team_tile(const uint32_t *__restrict__ ks, const
     const uint32_t j0 = kLaneKeys ? 8 * g : 512 * g + lane;  // the first of them
     const uint8_t *src = tin + 8 * (uint64_t)j0 + 4 * h;
     uint32_t w[8];
+    typedef unsigned int v4w __attribute__((ext_vector_type(4), aligned(4)));
+    v4w key[3];
+    if constexpr (kLaneKeys) {
 #pragma unroll
-    for (int r = 0; r < 8; r++) {
-        if constexpr (kMode == TileMode::kCtr) {
-            const uint64_t t = iv + first_block + j0 + kStep * r;  // wraps modulo 2^64
-            w[r] = h ? be_lo_word(t) : be_hi_word(t);
-        } else {
-            w[r] = 0;
-            if (j0 + kStep * r < n_valid) w[r] = *reinterpret_cast<const uint32_t *>(src + 8 * kStep * r);
+        for (int i = 0; i < 3; i++) key[i] = reinterpret_cast<const v4w *>(ks + 12 * wave)[i];
+    }
+    if constexpr (kLaneKeys) {
+        // The thread's eight blocks are 64 bytes in a row, in another line for every lane: two blocks a load.
+#pragma unroll
+        for (int r = 0; r < 8; r += 2) {
+            const uint8_t *p = tin + 8 * (uint64_t)(j0 + r);
+            v4u v = {0, 0, 0, 0};
+            if (j0 + r + 1 < n_valid) {
+                v = *reinterpret_cast<const v4u *>(p);
+            } else if (j0 + r < n_valid) {
+                const uint2 u = *reinterpret_cast<const uint2 *>(p);
+                v.x = u.x;
+                v.y = u.y;
+            }
+            w[r] = h ? v.y : v.x;
+            w[r + 1] = h ? v.w : v.z;
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < 8; r++) {
+            if constexpr (kMode == TileMode::kCtr) {
+                const uint64_t t = iv + first_block + j0 + kStep * r;  // wraps modulo 2^64
+                w[r] = h ? be_lo_word(t) : be_hi_word(t);
+            } else {
+                w[r] = 0;
+                if (j0 + kStep * r < n_valid) w[r] = *reinterpret_cast<const uint32_t *>(src + 8 * kStep * r);
+            }
         }
     }
     transpose8(w);
@@ -235,6 +262,13 @@ __device__ __forceinline__ void team_tile(const uint32_t *__restrict__ ks, const
     for (int p = 0; p < 32; p++) column[team_slot(p) * (4 * kLanes)] = (uint8_t)(w[p % 8] >> (p & 24));
 
     uint32_t *mine = lds + lane;
+    if constexpr (kLaneKeys) {
+        uint32_t *keys = lds + kTeamWords + lane;
+#pragma unroll
+        for (int i = 0; i < 12; i++) keys[kLanes * (12 * wave + i)] = key[i / 4][i % 4];
+        __syncthreads();
+        ks = keys;
+    }
     switch (wave) {
         case 0: team_rounds<0, kLaneKeys>(mine, ks); break;
         case 1: team_rounds<1, kLaneKeys>(mine, ks); break;

@@ -3,7 +3,7 @@ and of the plan that the device writes.
 
 Batches of 1152 and 1153 tiles, only lane tiles (with idle lanes in the last one), only whole tiles, one
 message long enough for several planning workgroups, messages whose last partial tile is a wave tile, and
-empty messages between others; through tdes_ecb_batch (launched and replayed from its graph) and
+empty messages between others, and both sides of the allocation-free batch's single launch; through tdes_ecb_batch (launched and replayed from its graph) and
 tdes_ecb_batch_static.  Expected output: the oracle's on every block of short messages and on the ends and
 a sample of long ones.  Bytes between the messages stay untouched.  Tolerance: 0 bits.
 """
@@ -27,6 +27,8 @@ SHAPES = {
     "wave remainders": [1800, 2047, 2048, 2049, 4096 + 1801],
     "one long message": [2048 * 700 + 77],
     "empty messages": [0, 40, 0, 0, 2048, 0],
+    "1024 jobs, one launch": [j % 70 for j in range(1024)],
+    "1025 jobs": [j % 70 for j in range(1025)],
     "1500 tiles, mixed": [2048 + 64 * (j % 30) for j in range(1000)],
 }
 
