@@ -54,13 +54,12 @@ hipError_t launch_table(const uint32_t *ks, const uint8_t *in, uint8_t *out, uin
                         hipStream_t stream, uint32_t threads = 0);
 hipError_t launch_bitslice(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks,
                            hipStream_t stream, uint32_t threads = 0);
-// Short messages (k_short.hip): one bit of f per lane.  n_blocks below 2^32.  CBC decryption also takes a
-// part of a message: in[0] is its block `first`, and with first > 0 the block before in[0] is read.
+// Short messages (k_short.hip): one bit of f per lane.  n_blocks below 2^32.
 hipError_t launch_short_ecb(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, hipStream_t stream);
 hipError_t launch_short_ctr(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, uint64_t iv,
                             hipStream_t stream);
-hipError_t launch_short_cbc_decrypt(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks,
-                                    uint64_t first, uint64_t iv, hipStream_t stream);
+hipError_t launch_short_cbc_decrypt(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, uint64_t iv,
+                                    hipStream_t stream);
 // Middling messages (k_team.hip): a workgroup per tile of 2048 blocks.  n_blocks below 2^42.
 hipError_t launch_team_ecb(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, hipStream_t stream);
 hipError_t launch_team_ctr(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, uint64_t iv,

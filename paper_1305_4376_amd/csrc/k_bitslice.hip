@@ -10,15 +10,16 @@
 // The kernel takes every whole 2048-block tile (16 KiB of the message, one
 // wave each); its code has only that path, so it fits 128 VGPRs and runs four
 // waves per SIMD.  Tiles beyond 2^22 per launch loop grid-stride.  A partial
-// last tile follows in the short-message kernel (k_short.hip): 3 us, where a
-// wave alone on it would take 33.  Buffers that are only 8-byte aligned take
-// the same path (3000001 blocks behind an 8-byte header: 43.4 us a call with
-// per-block accesses, 43.2 now, 3 of it the tail).  The key is the same for the whole launch,
-// so its masks come from scalar registers.
+// last tile runs beside the whole ones, one bit of f per lane (short_core.h):
+// a wave alone on it would take 33 us.  Buffers that are only 8-byte aligned
+// take the same path (3000001 blocks behind an 8-byte header: 43.4 us a call
+// with per-block accesses and a wave on the last block, 43.2 with 16-byte
+// accesses and the last block behind the others, 40.2 beside them).  The key
+// is the same for the whole launch, so its masks come from scalar registers.
 #include <hip/hip_runtime.h>
 
-#include "bitslice_core.h"
 #include "internal.h"
+#include "short_core.h"
 
 namespace {
 
@@ -45,6 +46,30 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void tdes_bitslice_kernel(
     }
 }
 
+// A message with a partial last tile: the first tail_groups workgroups take its last tail_blocks blocks one bit
+// of f per lane, beside the whole tiles of the others.  (An instance of its own, so that the code of the
+// kernel above stays what it is.)
+template <TileMode kMode>
+__global__ __launch_bounds__(kDefaultThreads, kWavesPerSimd) void tdes_bitslice_ragged_kernel(
+    const uint32_t *__restrict__ ks, const uint8_t *in, uint8_t *out, uint64_t n_tiles, uint64_t iv, uint32_t tail_blocks,
+    uint32_t tail_groups) {
+    static_assert(kDefaultThreads == kShortThreads, "one workgroup size for both parts");
+    if (blockIdx.x < tail_groups) {
+        const uint64_t done = n_tiles * kTileBlocks;
+        short_blocks<kMode>(ks, in + 8 * done, out + 8 * done, tail_blocks, blockIdx.x, true,
+                            kMode == TileMode::kCtr ? iv + done : iv);
+        return;
+    }
+    constexpr int kWaves = kDefaultThreads / kLanes;
+    const uint32_t lane = threadIdx.x % kLanes;
+    const uint64_t stride = (uint64_t)(gridDim.x - tail_groups) * kWaves;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+    for (uint64_t tile = (uint64_t)(blockIdx.x - tail_groups) * kWaves + wave; tile < n_tiles; tile += stride) {
+        const uint64_t first = tile * kTileBlocks;
+        mode_tile<kMode, true>(ks, in + 8 * first, out + 8 * first, kTileBlocks, lane, first, iv);
+    }
+}
+
 // ECB of a message shorter than a tile, by one wave: what TDES_VARIANT_BITSLICE asks for by name (36 us, where
 // the automatic choice takes 3).
 __global__ __launch_bounds__(kLanes) void tdes_bitslice_tail_kernel(const uint32_t *__restrict__ ks, const uint8_t *in,
@@ -62,23 +87,24 @@ hipError_t launch(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t 
                   hipStream_t stream) {
     constexpr int kWaves = kThreads / kLanes;
     const uint64_t whole = n_blocks / kTileBlocks, done = whole * kTileBlocks;
+    const uint32_t rest = (uint32_t)(n_blocks - done);
+    if (whole && rest && kThreads == kDefaultThreads) {
+        const uint32_t tail = short_groups(rest);
+        hipLaunchKernelGGL(tdes_bitslice_ragged_kernel<kMode>, dim3(tail + grid_for(whole, kWaves)), dim3(kThreads), 0,
+                           stream, ks, in, out, whole, iv, rest, tail);
+        return hipGetLastError();
+    }
     if (whole) {
         hipLaunchKernelGGL((tdes_bitslice_kernel<kMode, kThreads>), dim3(grid_for(whole, kWaves)), dim3(kThreads), 0,
                            stream, ks, in, out, whole, iv);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (done == n_blocks) return hipSuccess;
-    const uint8_t *tin = in + 8 * done;
-    uint8_t *tout = out + 8 * done;
-    if constexpr (kMode == TileMode::kEcb) {
-        if (whole) return tdes::launch_short_ecb(ks, tin, tout, n_blocks - done, stream);
-        hipLaunchKernelGGL(tdes_bitslice_tail_kernel, dim3(1), dim3(kLanes), 0, stream, ks, in, out, (uint32_t)n_blocks);
-        return hipGetLastError();
-    }
-    if constexpr (kMode == TileMode::kCtr)
-        return tdes::launch_short_ctr(ks, tin, tout, n_blocks - done, iv + done, stream);
-    return tdes::launch_short_cbc_decrypt(ks, tin, tout, n_blocks - done, done, iv, stream);
+    if (rest == 0) return hipSuccess;
+    // ECB with a workgroup size, or shorter than a tile (the modes come here with neither).
+    if (whole) return tdes::launch_short_ecb(ks, in + 8 * done, out + 8 * done, rest, stream);
+    hipLaunchKernelGGL(tdes_bitslice_tail_kernel, dim3(1), dim3(kLanes), 0, stream, ks, in, out, rest);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -108,7 +134,7 @@ hipError_t launch_ctr(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint6
 
 hipError_t launch_cbc_decrypt(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, uint64_t iv,
                               hipStream_t stream) {
-    if (n_blocks < kShortBelow) return launch_short_cbc_decrypt(ks, in, out, n_blocks, 0, iv, stream);
+    if (n_blocks < kShortBelow) return launch_short_cbc_decrypt(ks, in, out, n_blocks, iv, stream);
     if (n_blocks <= kPairAgainTo) return launch_pair_cbc_decrypt(ks, in, out, n_blocks, iv, stream);
     if (n_blocks < kTeamBelow) return launch_team_cbc_decrypt(ks, in, out, n_blocks, iv, stream);
     return launch<TileMode::kCbcDecrypt>(ks, in, out, n_blocks, iv, stream);
