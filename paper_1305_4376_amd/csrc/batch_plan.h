@@ -58,10 +58,10 @@ hipError_t launch_batch_capped(const uint32_t *sched, const PlanHeader *hdr, con
                                uint8_t *base, uint32_t grid, uint32_t threads, uint32_t tiles_per_draw,
                                hipStream_t stream);
 
-// A batch of at most kTeamTiles tiles: a workgroup per tile (k_batch_team.hip).  The line is the plain
-// message's (kTeamBelow): the team takes 23 us for 234 tiles (18 of them lane tiles), 34 for 978 and 40 for
-// 1150, a wave per tile 46 and upwards for any batch with lane tiles and 55 for 1466 tiles.
-constexpr uint32_t kTeamTiles = 1152;
+// A batch of at most kTeamTiles tiles: a workgroup per tile (k_batch_team.hip).  Launches back to back, us, by
+// teams / by waves: 1152 whole tiles 41 / -, 1400 46 / 53, 2000 58 / 60, 2300 65 / 63; with lane tiles among
+// them 234 (18 of them) 22.5 / 46, 1466 (239) 48 / 55, 1949 (313) 60 / 60.
+constexpr uint32_t kTeamTiles = 2048;
 hipError_t launch_batch_team(const uint32_t *sched, const PlanHeader *hdr, const Slot *slots, uint8_t *base,
                              uint32_t grid, hipStream_t stream);  // grid: at least the tiles
 

@@ -8,25 +8,24 @@
 // device array per GPU, `scratch`, whose address is looked up once per device
 // with hipGetSymbolAddress and passed to the kernels from then on.
 //
-// Few jobs in a small buffer (kSmallJobs; the buffer bounds the tiles): one launch.  Every workgroup reads all
-// jobs, counts and sums their tiles in LDS, and takes the tiles of its turn with its eight waves (team_core.h):
-// wave tiles of up to 2048 blocks of one job, and lane tiles of 64 slots of up to 32 blocks, from the jobs'
-// remainders.  512 jobs of up to 8192 blocks (658 tiles by job, 234 packed): 29.8 us a call with the
-// launches below, 22.0 so.
+// Up to kSmallJobs jobs: one or two launches on the caller's stream.
+//   small  -- every workgroup reads all jobs, rejects any that is malformed or reaches outside
+//             [dev_base, dev_base + base_bytes) (it gets no tiles), and counts and sums their tiles in LDS:
+//             wave tiles of up to 2048 blocks of one job, and lane tiles of 64 slots of up to 32 blocks, from
+//             the jobs' remainders.  If there are at most kStaticTeamTiles, the workgroups work them off with their
+//             eight waves (team_core.h); if not, the first workgroup leaves the plan below in scratch;
+//   cipher -- launched unless the buffer's size rules out more tiles than that; ends at once if the small
+//             kernel did the work.
+// 512 jobs of up to 8192 blocks (658 tiles by job, 234 packed): 46 us a call by plan and cipher, 22.9 by the
+// small kernel; 2048 jobs of up to 256 blocks 68 and 23.7.
 //
-// Otherwise three launches on the caller's stream:
-//   plan   -- one workgroup reads the jobs, rejects any that is malformed or
-//             reaches outside [dev_base, dev_base + base_bytes) (it gets no
-//             tiles), and writes the exclusive prefix sum of wave tiles (2048
-//             blocks each) per job into scratch, the tile total, the number of
+// More jobs: two launches.
+//   plan   -- one workgroup reads and checks the jobs and writes the exclusive prefix sum of wave tiles (2048
+//             blocks each, a job's last one partial) per job into scratch, the tile total, the number of
 //             rejected jobs, and a zeroed tile counter;
-//   team   -- if there are at most kTeamTiles tiles, a workgroup per tile;
-//   cipher -- otherwise persistent waves that draw tiles (the first by wave
-//             index, later ones from the counter) and run the bitsliced core on them, with the
-//             job's key masks in scalar registers.
-// Both find each tile's job by binary search over the prefix sums; only the device knows how many tiles
-// there are, so both are launched and one of them ends at once (4 us).  A job's last tile may be
-// partial: its blocks take the core's per-block path.
+//   cipher -- persistent waves draw tiles (the first by wave index, later ones from the counter), find each
+//             tile's job by binary search over the prefix sums and run the bitsliced core on it, with the
+//             job's key masks in scalar registers.  A partial tile takes the core's per-block path.
 // Nothing here carries state from one call to the next except scratch, which
 // the plan launch rewrites before the cipher launch reads it.
 #include <stdint.h>
@@ -34,7 +33,6 @@
 #include <atomic>
 #include <mutex>
 
-#include "batch_plan.h"
 #include "internal.h"
 #include "team_core.h"
 
@@ -47,7 +45,10 @@ constexpr uint32_t kPlanThreads = 1024;
 constexpr uint32_t kThreads = 256;
 constexpr uint32_t kGroupsPerCU = 4;
 constexpr uint64_t kMaxJobBlocks = 1ull << 40;
-constexpr uint32_t kSmallJobs = 2 * kTeamThreads;  // two per thread
+// Teams up to here, waves from there on: 1400 tiles 57.6 us by the small kernel and 58.1 by two, 1700 59.6 and
+// 60.6, 2000 65.4 and 64.8.
+constexpr uint32_t kStaticTeamTiles = 1600;
+constexpr uint32_t kSmallJobs = 4096;              // eight per thread of a team
 constexpr uint32_t kLaneBlocks = 32;
 constexpr uint32_t kWaveRemainder = 1800;          // a remainder of at least this many blocks is a wave tile
 
@@ -175,17 +176,6 @@ __device__ __forceinline__ StaticTile find_tile(uint32_t ticket, const tdes_job 
     return t;
 }
 
-__global__ __launch_bounds__(kTeamThreads) void tdes_static_team_kernel(const tdes_job *__restrict__ jobs, uint32_t n_jobs,
-                                                                        const uint32_t *__restrict__ sched, uint8_t *scr,
-                                                                        uint8_t *base) {
-    __shared__ uint32_t lds[kTeamWords];
-    const uint32_t n_tiles = reinterpret_cast<const StaticHeader *>(scr)->n_tiles;
-    if (n_tiles > tdes::kTeamTiles || blockIdx.x >= n_tiles) return;
-    const StaticTile t = find_tile(blockIdx.x, jobs, n_jobs, sched,
-                                   reinterpret_cast<const uint32_t *>(scr + sizeof(StaticHeader)), base);
-    team_tile<TileMode::kEcb, false>(t.ks, t.in, t.out, t.count, threadIdx.x, 0, 0, lds);
-}
-
 __global__ __launch_bounds__(kThreads, kGroupsPerCU) void tdes_static_batch_kernel(
     const tdes_job *__restrict__ jobs, uint32_t n_jobs, const uint32_t *__restrict__ sched, uint8_t *scr,
     uint8_t *base) {
@@ -193,7 +183,6 @@ __global__ __launch_bounds__(kThreads, kGroupsPerCU) void tdes_static_batch_kern
     const uint32_t *tile_start = reinterpret_cast<const uint32_t *>(scr + sizeof(StaticHeader));
     const uint32_t lane = threadIdx.x % kLanes;
     const uint32_t n_tiles = __builtin_amdgcn_readfirstlane(hdr->n_tiles);
-    if (n_tiles <= tdes::kTeamTiles) return;
     const uint32_t n_waves = gridDim.x * (blockDim.x / kLanes);
     const uint32_t wave_id = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x / kLanes) + threadIdx.x / kLanes);
     for (uint32_t ticket = wave_id; ticket < n_tiles; ticket = next_ticket(&hdr->counter, n_waves, lane)) {
@@ -205,77 +194,127 @@ __global__ __launch_bounds__(kThreads, kGroupsPerCU) void tdes_static_batch_kern
     }
 }
 
-// The whole call by teams, without a plan in memory.  n_jobs <= kSmallJobs, and base_bytes so small that the
-// sums below fit 32 bits.
+// A job's wave tiles and lane slots; both 0 if it is refused.
+struct JobTiles {
+    uint32_t wave, slots;
+};
+__device__ __forceinline__ JobTiles job_tiles(const tdes_job &x, bool ok) {
+    JobTiles t{0, 0};
+    if (!ok) return t;
+    const uint32_t rem = (uint32_t)(x.n_blocks % kTileBlocks), wave_rem = rem >= kWaveRemainder;
+    t.wave = (uint32_t)(x.n_blocks / kTileBlocks) + wave_rem;
+    if (!wave_rem) t.slots = (rem + kLaneBlocks - 1) / kLaneBlocks;
+    return t;
+}
+
+// The whole call by teams if its tiles are few, else its plan.  n_jobs <= kSmallJobs.  alone: no cipher kernel
+// follows; scratch is not touched, and every tile is the teams' (base_bytes is then below 2^24, and the sums
+// fit 32 bits).
 __global__ __launch_bounds__(kTeamThreads) void tdes_static_small_kernel(const tdes_job *__restrict__ jobs, uint32_t n_jobs,
                                                                          const uint32_t *__restrict__ sched,
-                                                                         uint64_t n_scheds, uint8_t *base,
-                                                                         uint64_t base_bytes, uint32_t *dev_rejected) {
+                                                                         uint64_t n_scheds, uint8_t *scr, uint8_t *base,
+                                                                         uint64_t base_bytes, uint32_t *dev_rejected,
+                                                                         bool alone) {
     __shared__ uint32_t lds[kTeamLaneWords];
-    __shared__ uint32_t wave_start[kSmallJobs + 1], lane_start[kSmallJobs + 1];  // exclusive sums over the jobs
-    __shared__ uint32_t part_wave[8], part_lane[8], part_bad[8];
+    __shared__ uint32_t wave_start[kTeamThreads], lane_start[kTeamThreads];  // exclusive sums, by thread's group of jobs
+    __shared__ uint64_t part_wave[8];
+    __shared__ uint32_t part_lane[8], part_ragged[8], part_bad[8];
     const uint32_t tid = threadIdx.x, lane = tid % kLanes, wv = tid / kLanes;
-    uint32_t wave[2], slots[2], bad = 0;
-#pragma unroll
-    for (int i = 0; i < 2; i++) {
-        wave[i] = slots[i] = 0;
-        if (2 * tid + i < n_jobs) {
-            const tdes_job x = jobs[2 * tid + i];
-            if (job_ok(x, n_scheds, base_bytes)) {
-                const uint32_t rem = (uint32_t)(x.n_blocks % kTileBlocks), wave_rem = rem >= kWaveRemainder;
-                wave[i] = (uint32_t)(x.n_blocks / kTileBlocks) + wave_rem;
-                if (!wave_rem) slots[i] = (rem + kLaneBlocks - 1) / kLaneBlocks;
-            } else {
-                bad++;
-            }
-        }
+    const uint32_t per = (n_jobs + kTeamThreads - 1) / kTeamThreads;
+    // the thread's jobs: wave tiles, lane slots, jobs with lane slots, refused jobs
+    uint64_t wave = 0;
+    uint32_t slots = 0, ragged = 0, bad = 0;
+    for (uint32_t j = tid * per; j < min(n_jobs, (tid + 1) * per); j++) {
+        const tdes_job x = jobs[j];
+        const bool ok = job_ok(x, n_scheds, base_bytes);
+        const JobTiles t = job_tiles(x, ok);
+        wave += t.wave;
+        slots += t.slots;
+        ragged += t.slots != 0;
+        bad += !ok;
     }
-    // inclusive sums of both counts over the wave's threads, then over the waves
-    uint32_t w = wave[0] + wave[1], s = slots[0] + slots[1];
+    // inclusive sums over the wave's threads, then over the waves
+    uint64_t w = wave;
+    uint32_t s = slots, g = ragged;
 #pragma unroll
     for (int d = 1; d < kLanes; d <<= 1) {
-        const uint32_t pw = __shfl_up(w, d), ps = __shfl_up(s, d);
-        if ((int)lane >= d) { w += pw; s += ps; }
+        const uint64_t pw = __shfl_up((unsigned long long)w, d);
+        const uint32_t ps = __shfl_up(s, d), pg = __shfl_up(g, d);
+        if ((int)lane >= d) { w += pw; s += ps; g += pg; }
     }
 #pragma unroll
     for (int d = 1; d < kLanes; d <<= 1) bad += __shfl_xor(bad, d);
-    if (lane == kLanes - 1) { part_wave[wv] = w; part_lane[wv] = s; part_bad[wv] = bad; }
+    if (lane == kLanes - 1) { part_wave[wv] = w; part_lane[wv] = s; part_ragged[wv] = g; part_bad[wv] = bad; }
     __syncthreads();
-    uint32_t all_wave = 0, all_slots = 0, all_bad = 0;
+    uint64_t all_wave = 0;
+    uint32_t all_slots = 0, all_ragged = 0, all_bad = 0;
 #pragma unroll
     for (uint32_t i = 0; i < 8; i++) {
-        if (i < wv) { w += part_wave[i]; s += part_lane[i]; }
+        if (i < wv) { w += part_wave[i]; s += part_lane[i]; g += part_ragged[i]; }
         all_wave += part_wave[i];
         all_slots += part_lane[i];
+        all_ragged += part_ragged[i];
         all_bad += part_bad[i];
     }
-    wave_start[2 * tid + 2] = w;
-    wave_start[2 * tid + 1] = w - wave[1];
-    lane_start[2 * tid + 2] = s;
-    lane_start[2 * tid + 1] = s - slots[1];
-    if (tid == 0) {
-        wave_start[0] = lane_start[0] = 0;
-        if (blockIdx.x == 0 && dev_rejected) *dev_rejected = all_bad;
+    const uint64_t by_job = all_wave + all_ragged;  // the cipher kernel's tiles: a remainder is a tile of its own
+    const bool overflow = by_job >= (1ull << 31);
+    const uint32_t n_lane_tiles = (all_slots + kLanes - 1) / kLanes;
+    const bool mine = alone || all_wave + n_lane_tiles <= kStaticTeamTiles;
+    if (blockIdx.x == 0 && tid == 0 && dev_rejected) *dev_rejected = overflow ? n_jobs : all_bad;
+    if (blockIdx.x == 0 && !alone) {
+        StaticHeader *hdr = reinterpret_cast<StaticHeader *>(scr);
+        uint32_t *tile_start = reinterpret_cast<uint32_t *>(scr + sizeof(StaticHeader));
+        if (tid == 0) {
+            hdr->n_tiles = mine || overflow ? 0 : (uint32_t)by_job;
+            hdr->rejected = overflow ? n_jobs : all_bad;
+            hdr->counter = 0;
+        }
+        if (!mine && !overflow) {
+            uint32_t run = (uint32_t)(w - wave) + (g - ragged);
+            for (uint32_t j = tid * per; j < min(n_jobs, (tid + 1) * per); j++) {
+                const tdes_job x = jobs[j];
+                tile_start[j] = run;
+                if (job_ok(x, n_scheds, base_bytes)) run += (uint32_t)((x.n_blocks + kTileBlocks - 1) / kTileBlocks);
+            }
+            if (tid == 0) tile_start[n_jobs] = (uint32_t)by_job;
+        }
     }
+    if (!mine) return;
+    wave_start[tid] = (uint32_t)(w - wave);
+    lane_start[tid] = s - slots;
     __syncthreads();
 
-    const uint32_t n_lane_tiles = (all_slots + kLanes - 1) / kLanes, n_tiles = n_lane_tiles + all_wave;
+    // The job of wave tile (lane slot) `at`, and `at` within the job: the last group that starts at or before
+    // it, by binary search, then along the group.
+    auto find = [&](const uint32_t *start, uint32_t at, bool slots, tdes_job *job) {
+        uint32_t lo = 0, hi = kTeamThreads;
+        while (hi - lo > 1) {
+            const uint32_t mid = (lo + hi) / 2;
+            if (start[mid] <= at) lo = mid; else hi = mid;
+        }
+        at -= start[lo];
+        for (uint32_t j = lo * per; j < n_jobs; j++) {
+            *job = jobs[j];
+            const JobTiles t = job_tiles(*job, job_ok(*job, n_scheds, base_bytes));
+            const uint32_t n = slots ? t.slots : t.wave;
+            if (at < n) break;
+            at -= n;
+        }
+        return at;
+    };
+    const uint32_t n_tiles = n_lane_tiles + (uint32_t)all_wave;
     for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
         if (tile < n_lane_tiles) {
-            // The lane's slot: of the last job that starts at or before it.  Lanes past the end stay idle.
+            // Lanes past the last slot stay idle.
             const uint32_t slot = tile * kLanes + lane;
             const uint32_t *ks = sched;
             const uint8_t *in = base;
             uint8_t *out = base;
             uint32_t count = 0;
             if (slot < all_slots) {
-                uint32_t lo = 0, hi = n_jobs;
-                while (hi - lo > 1) {
-                    const uint32_t mid = (lo + hi) / 2;
-                    if (lane_start[mid] <= slot) lo = mid; else hi = mid;
-                }
-                const tdes_job x = jobs[lo];
-                const uint32_t rem = (uint32_t)(x.n_blocks % kTileBlocks), at = kLaneBlocks * (slot - lane_start[lo]);
+                tdes_job x;
+                const uint32_t at = kLaneBlocks * find(lane_start, slot, true, &x);
+                const uint32_t rem = (uint32_t)(x.n_blocks % kTileBlocks);
                 const uint64_t first = x.n_blocks - rem + at;
                 ks = sched + (uint64_t)x.sched_idx * (TDES_SCHED_BYTES / 4) + x.direction * tdes::kDirWords;
                 in = base + x.in_off + 8 * first;
@@ -284,8 +323,12 @@ __global__ __launch_bounds__(kTeamThreads) void tdes_static_small_kernel(const t
             }
             team_tile<TileMode::kEcb, true>(ks, in, out, count, tid, 0, 0, lds);
         } else {
-            const StaticTile t = find_tile(tile - n_lane_tiles, jobs, n_jobs, sched, wave_start, base);
-            team_tile<TileMode::kEcb, false>(t.ks, t.in, t.out, t.count, tid, 0, 0, lds);
+            tdes_job x;
+            const uint64_t first = (uint64_t)__builtin_amdgcn_readfirstlane(find(wave_start, tile - n_lane_tiles, false, &x)) * kTileBlocks;
+            const uint32_t *ks = sched + (uint64_t)__builtin_amdgcn_readfirstlane(x.sched_idx) * (TDES_SCHED_BYTES / 4) +
+                                 __builtin_amdgcn_readfirstlane(x.direction) * tdes::kDirWords;
+            team_tile<TileMode::kEcb, false>(ks, base + uniform64(x.in_off) + 8 * first, base + uniform64(x.out_off) + 8 * first,
+                                             tile_count(uniform64(x.n_blocks) - first), tid, 0, 0, lds);
         }
         __syncthreads();
     }
@@ -334,23 +377,25 @@ extern "C" int tdes_ecb_batch_static(const tdes_job *dev_jobs, uint32_t n_jobs, 
     if (tdes::device_info(&info) != TDES_OK) return TDES_ERR_HIP;
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint8_t *base = static_cast<uint8_t *>(dev_base);
-    // Inputs and outputs of different jobs share no bytes, so the buffer bounds the tiles.  (A call that breaks
-    // that rule is still worked off: the workgroups take as many turns as there are tiles.)
-    const uint64_t most_tiles = base_bytes / (8 * kTileBlocks) + n_jobs;
-    if (n_jobs <= kSmallJobs && most_tiles <= tdes::kTeamTiles) {
-        const uint32_t resident = (uint32_t)info.cu_count * 3;  // 48 KiB of LDS per workgroup
+    const uint32_t *table = static_cast<const uint32_t *>(dev_sched_table);
+    if (n_jobs <= kSmallJobs) {
+        // Outputs of different jobs share no bytes, so the buffer bounds the tiles: a wave tile has at least
+        // kWaveRemainder blocks, a lane slot kLaneBlocks but for a job's last.  (If a call breaks that rule, the
+        // teams still work off what they have counted.)
+        const uint64_t most_tiles = base_bytes / (8 * kWaveRemainder) + n_jobs / kLanes + 2;
+        const bool alone = most_tiles <= kStaticTeamTiles;
+        const uint32_t resident = (uint32_t)info.cu_count * 3;  // 45 KiB of LDS per workgroup
         hipLaunchKernelGGL(tdes_static_small_kernel, dim3(most_tiles < resident ? (uint32_t)most_tiles : resident),
-                           dim3(kTeamThreads), 0, s, dev_jobs, n_jobs, static_cast<const uint32_t *>(dev_sched_table),
-                           n_scheds, base, base_bytes, dev_rejected);
-        return hipGetLastError() == hipSuccess ? TDES_OK : TDES_ERR_HIP;
+                           dim3(kTeamThreads), 0, s, dev_jobs, n_jobs, table, n_scheds, scr, base, base_bytes, dev_rejected,
+                           alone);
+        if (hipGetLastError() != hipSuccess) return TDES_ERR_HIP;
+        if (alone) return TDES_OK;
+    } else {
+        hipLaunchKernelGGL(tdes_static_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, dev_jobs, n_jobs, n_scheds,
+                           base_bytes, scr, dev_rejected);
+        if (hipGetLastError() != hipSuccess) return TDES_ERR_HIP;
     }
-    hipLaunchKernelGGL(tdes_static_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, dev_jobs, n_jobs, n_scheds,
-                       base_bytes, scr, dev_rejected);
-    if (hipGetLastError() != hipSuccess) return TDES_ERR_HIP;
-    hipLaunchKernelGGL(tdes_static_team_kernel, dim3(tdes::kTeamTiles), dim3(kTeamThreads), 0, s, dev_jobs, n_jobs,
-                       static_cast<const uint32_t *>(dev_sched_table), scr, base);
-    if (hipGetLastError() != hipSuccess) return TDES_ERR_HIP;
     hipLaunchKernelGGL(tdes_static_batch_kernel, dim3((uint32_t)info.cu_count * kGroupsPerCU), dim3(kThreads), 0, s,
-                       dev_jobs, n_jobs, static_cast<const uint32_t *>(dev_sched_table), scr, base);
+                       dev_jobs, n_jobs, table, scr, base);
     return hipGetLastError() == hipSuccess ? TDES_OK : TDES_ERR_HIP;
 }

@@ -1,7 +1,7 @@
 """GPU parity of batches on both sides of the switch between a workgroup per tile and a wave per tile,
 and of the plan that the device writes.
 
-Batches of 1152 and 1153 tiles, only lane tiles (with idle lanes in the last one), only whole tiles, one
+Batches of 1600 and 2048 tiles and of one more, only lane tiles (with idle lanes in the last one), only whole tiles, one
 message long enough for several planning workgroups, messages whose last partial tile is a wave tile, and
 empty messages between others, and both sides of the allocation-free batch's single launch; through tdes_ecb_batch (launched and replayed from its graph) and
 tdes_ecb_batch_static.  Expected output: the oracle's on every block of short messages and on the ends and
@@ -20,15 +20,17 @@ pytestmark = pytest.mark.gpu
 
 N_KEYS = 7
 SHAPES = {
-    "1152 whole tiles": [2048 * 3] * 384,
-    "1153 tiles": [2048 * 3] * 384 + [1900],
+    "1600 whole tiles": [2048 * 4] * 400,
+    "1601 tiles": [2048 * 4] * 400 + [1900],
+    "2048 whole tiles": [2048 * 4] * 512,
+    "2049 tiles": [2048 * 4] * 512 + [1900],
     "one lane": [5],
     "lane tiles, the last with idle lanes": [1, 31, 32, 33, 64, 1799] * 40,
     "wave remainders": [1800, 2047, 2048, 2049, 4096 + 1801],
     "one long message": [2048 * 700 + 77],
     "empty messages": [0, 40, 0, 0, 2048, 0],
-    "1024 jobs, one launch": [j % 70 for j in range(1024)],
-    "1025 jobs": [j % 70 for j in range(1025)],
+    "4096 jobs, one launch": [j % 40 for j in range(4096)],
+    "4097 jobs": [j % 40 for j in range(4097)],
     "1500 tiles, mixed": [2048 + 64 * (j % 30) for j in range(1000)],
 }
 
