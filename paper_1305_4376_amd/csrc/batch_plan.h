@@ -23,9 +23,8 @@ struct PlanMessage {
     uint32_t wave_first;
     uint32_t lane_first;
     uint32_t wave_tiles;
-    uint64_t pad[3];
 };
-static_assert(sizeof(PlanMessage) == 64, "one line of host memory");
+static_assert(sizeof(PlanMessage) == 40, "no padding: the records cross the host link");
 
 // A run of consecutive blocks of one message: byte offsets from the batch base,
 // the number of blocks (a wave tile: up to 2048; a lane slot: up to 32; 0 for
