@@ -1,7 +1,7 @@
 """Generate the bitsliced kernel's S-box circuits (csrc/sbox_circuits.inc).
 
     python -m paper_1305_4376_amd.gen.gen_sbox [--search TRIALS] [--budget N] [--seeds K] [--width W]
-                                               [--lns ITERATIONS]
+                                               [--lns ITERATIONS] [--walk STEPS] [--slack N]
 
 Each of the eight DES S-boxes (read from csrc/des_spec.h, the table the other
 kernel uses too) becomes a function of six bit planes that XORs its four
@@ -10,11 +10,13 @@ any Boolean function of three 32-bit words, given as an 8-bit truth table
 whose bit (4a + 2b + c) is the output for operand bits a, b, c.
 
 The circuits come from sbox_search.c (a randomized decomposition search
-written for this purpose; see that file).  The chosen ones are stored in
+written for this purpose) and, from its circuits, sbox_walk.c (a random walk
+over correct circuits); see those files.  The chosen ones are stored in
 sbox_circuits.txt; with --search the search runs again and a circuit replaces
 the stored one only if it has fewer gates (then a lower cost).  --lns runs
-the search's large-neighbourhood mode from each stored circuit.  Every
-circuit is checked on all 64 inputs before any code is written.
+the search's large-neighbourhood mode from each stored circuit, --walk the
+walk (about 30000 steps a second).  Every circuit is checked on all 64 inputs
+before any code is written.
 """
 from __future__ import annotations
 
@@ -32,6 +34,7 @@ SPEC = os.path.join(PKG, "csrc", "des_spec.h")
 OUT_INC = os.path.join(PKG, "csrc", "sbox_circuits.inc")
 STORE = os.path.join(HERE, "sbox_circuits.txt")
 SEARCH_SRC = os.path.join(HERE, "sbox_search.c")
+WALK_SRC = os.path.join(HERE, "sbox_walk.c")
 
 MASK64 = (1 << 64) - 1
 
@@ -134,7 +137,7 @@ def load_store(path: str = STORE) -> dict[int, Circuit]:
 
 def save_store(circuits: dict[int, Circuit], path: str = STORE):
     with open(path, "w") as f:
-        f.write("# S-box circuits of 3-input lookup gates, found by sbox_search.c; see gen_sbox.py.\n")
+        f.write("# S-box circuits of 3-input lookup gates, found by sbox_search.c and sbox_walk.c; see gen_sbox.py.\n")
         f.write("# Nodes 0..5 are the box inputs (0 = first); 'g node a b c table'; 'out' lists the nodes\n")
         f.write("# of output bits 1..4 (an output may be the complement of its node).\n")
         for b in sorted(circuits):
@@ -160,7 +163,7 @@ def last_circuit(text: str) -> Circuit | None:
 
 
 def run_from(exe, args, tab, circuit: Circuit) -> Circuit | None:
-    """Feed a stored circuit to the search's large-neighbourhood mode; return the last circuit it printed, or None."""
+    """Feed a stored circuit to the walk or the search's large-neighbourhood mode; return the last circuit it printed, or None."""
     res = subprocess.run([exe] + [str(a) for a in args] + [str(v) for v in tab], input=circuit.dump(),
                          stdout=subprocess.PIPE, stderr=subprocess.DEVNULL, text=True)
     if res.returncode != 0 or "\n" not in res.stdout:
@@ -231,6 +234,8 @@ def main():
     ap.add_argument("--seeds", type=int, default=8)
     ap.add_argument("--width", type=int, default=1, help="search: attempts per output, best kept")
     ap.add_argument("--lns", type=int, default=0, help="iterations of the search's large-neighbourhood mode (0: none)")
+    ap.add_argument("--walk", type=int, default=0, help="steps of the random walk per seed (0: none)")
+    ap.add_argument("--slack", type=int, default=2, help="walk: gates above the smallest circuit so far")
     ap.add_argument("--boxes", default="1,2,3,4,5,6,7,8")
     ap.add_argument("--store", default=STORE, help="circuit store to read and update")
     ap.add_argument("--out", default=OUT_INC, help="generated HIP include")
@@ -267,7 +272,15 @@ def main():
                 circuits[bs[0]])), jobs))
         for b, c in results:
             accept(b, c, "large-neighbourhood search")
-    if args.search or args.lns:
+    if args.walk:
+        exe = build_tool(WALK_SRC)
+        jobs = [(b, s) for b in todo if b in circuits for s in range(args.seeds)]
+        with ThreadPoolExecutor(max_workers=workers) as pool:
+            results = list(pool.map(lambda bs: (bs[0], run_from(
+                exe, [9000 * bs[0] + bs[1] + 1, args.walk, args.slack], boxes[bs[0]], circuits[bs[0]])), jobs))
+        for b, c in results:
+            accept(b, c, "walk")
+    if args.search or args.lns or args.walk:
         save_store(circuits, args.store)
     missing = [b + 1 for b in range(8) if b not in circuits]
     if missing:
