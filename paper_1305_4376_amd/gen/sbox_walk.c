@@ -136,6 +136,34 @@ static int separates(tt on, tt off, tt a, tt b, tt c) {
     return 1;
 }
 
+/* A filter for separates: 64 pairs of a point of `on` and a point of `off` drawn at random, every pair inside one
+   of the cells given; apart[i]: the pairs that candidate i tells apart.  A gate can only separate if its three
+   operands tell all pairs apart between them.  Returns 0 if no cell has both kinds of points. */
+static int sample_pairs(const circuit_t *C, const int *cand, int n, const tt *on, const tt *off, int cells, uint64_t *apart) {
+    int point[2][64], count[2] = {0, 0}, mixed[4], n_mixed = 0, p[64], q[64];
+    for (int m = 0; m < cells; m++)
+        if (on[m] && off[m]) mixed[n_mixed++] = m;
+    if (n_mixed == 0) return 0;
+    for (int t = 0; t < 64; t++) {
+        if (t % (64 / n_mixed) == 0 && t / (64 / n_mixed) < n_mixed) {
+            const int m = mixed[t / (64 / n_mixed)];
+            count[0] = count[1] = 0;
+            for (tt x = on[m]; x; x &= x - 1) point[0][count[0]++] = __builtin_ctzll(x);
+            for (tt x = off[m]; x; x &= x - 1) point[1][count[1]++] = __builtin_ctzll(x);
+        }
+        const uint64_t r = rnd();
+        p[t] = point[0][(r & 0xffffffff) % (unsigned)count[0]];
+        q[t] = point[1][(r >> 32) % (unsigned)count[1]];
+    }
+    for (int i = 0; i < n; i++) {
+        const tt v = C->v[cand[i]];
+        uint64_t a = 0;
+        for (int t = 0; t < 64; t++) a |= ((v >> p[t] ^ v >> q[t]) & 1) << t;
+        apart[i] = a;
+    }
+    return 1;
+}
+
 /* Such a gate; cells without a requirement at random. */
 static gate_t make_gate(const circuit_t *C, tt on, tt off, int a, int b, int c) {
     gate_t g = {{a, b, c}, 0};
@@ -186,9 +214,12 @@ static int rewire(circuit_t *C, int k) {
     }
     const int want = 1 + rndint(24); /* one of the first few in a random order */
     int found = 0, pick[3] = {0, 0, 0};
+    uint64_t apart[MAXN];
+    if (!sample_pairs(C, cand, n, &on, &off, 1, apart)) return 0;
     for (int a = 0; a < n && found < want; a++)
         for (int b = a + 1; b < n && found < want; b++)
             for (int c = b + 1; c < n && found < want; c++) {
+                if (~(apart[a] | apart[b] | apart[c])) continue;
                 if (!separates(on, off, C->v[cand[a]], C->v[cand[b]], C->v[cand[c]])) continue;
                 if (rndint(++found) == 0) {
                     pick[0] = cand[a];
@@ -270,10 +301,13 @@ static int rebuild(circuit_t *C, int k, int pairs, int limit) {
             on4[m] = mixed ? on & x : 0;
             off4[m] = mixed ? off & x : 0;
         }
+        uint64_t apart[MAXN];
+        if (!sample_pairs(C, cand, n, on4, off4, 4, apart)) continue;
         for (int i = 0; i < n; i++)
             for (int a = (i + start) % n, b = 0; b < a; b++)
                 for (int c = 0; c < b; c++) {
                     int pol[4];
+                    if (~(apart[a] | apart[b] | apart[c])) continue;
                     if (!parity_gate(on4, off4, C->v[cand[a]], C->v[cand[b]], C->v[cand[c]], pol)) continue;
                     tt g_on = 0, g_off = 0;
                     for (int m = 0; m < 4; m++) {
