@@ -353,7 +353,7 @@ def bench_paper_scheme(td, torch, sched, dev):
         rows.append({"blocks_per_launch": chunk, "launches": launches, "seconds": round(dt, 5),
                      "gbs": round(total * 8 / dt / 1e9, 3), "extrapolated": timed < launches})
     return {"workload": "512 MiB message, in place, one launch per chunk (Listing 1.1's loop, issued by "
-                        "tdes_ecb_chunked; table kernel below 2^20 blocks per chunk, bitsliced from there)",
+                        "tdes_ecb_chunked, which picks the kernel by the chunk's size)",
             "rows": rows}
 
 
@@ -450,8 +450,8 @@ def bench_c3(td, torch, inputs, dev):
                                   reps=5 if log_n >= 29 else 20)
                 rows.append({"keying": keying, "blocks": n, "direction": "decrypt" if d else "encrypt",
                              "us": round(t * 1e6, 2), "gbs": round(n * 8 / t / 1e9, 3)})
-    return {"workload": "keying x size x direction, the automatic variant (table below 2^20 blocks, bitsliced "
-                        "from there), one launch each, kernel-only", "rows": rows}
+    return {"workload": "keying x size x direction, the automatic variant (the kernel picked by size), "
+                        "one launch each, kernel-only", "rows": rows}
 
 
 def bench_paper_threads(td, torch, dev):

@@ -208,7 +208,7 @@ typedef struct tdes_batch_info {
     uint64_t tiles;          /* work items of the last batch */
     uint64_t wave_tiles;     /* ... of up to 2048 blocks of one message */
     uint64_t lane_tiles;     /* ... of 64 lane slots of up to 32 blocks */
-    uint64_t slots;          /* slot descriptors uploaded */
+    uint64_t slots;          /* slot descriptors of the plan */
     uint64_t blocks;         /* message blocks in the batch */
     uint64_t padded_blocks;  /* block positions computed (tiles x 2048) */
     uint32_t threads;        /* threads per workgroup of the batch kernel */

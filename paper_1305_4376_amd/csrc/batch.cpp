@@ -1,10 +1,11 @@
-// batch.cpp -- batched ECB: validation, tile planning, plan upload, graph capture, tuning.
+// batch.cpp -- batched ECB: validation, tile planning, graph capture, tuning.
 //
 // A batch is many messages, each with its own key triple (an index into a
 // device table of schedules) and direction.  The paper runs one message and
 // launches one kernel per 1 MiB chunk (Listing 1.1, Section II.B); with
 // thousands of short messages, per-launch cost would dominate, so the whole
-// batch becomes one launch of the persistent kernel in k_batch.hip.
+// batch becomes one launch: of the persistent kernel in k_batch.hip, or of
+// k_batch_team.hip's for few tiles.
 //
 // Planning.  Each message is cut into wave tiles of 2048 blocks (one key per
 // wave, scalar key masks).  Its remainder, if shorter than the context's

@@ -2,8 +2,8 @@
 //
 // The paper's host loop launches one kernel per 1 MiB chunk and finds the
 // launch granularity matters (Section II.B and Table II).  Here a whole batch
-// of messages of any lengths is one launch: the host cuts the work into tiles
-// (batch.cpp) and a fixed grid of waves draws tiles from an atomic counter
+// of messages of any lengths is one launch: the work is cut into tiles
+// (batch.cpp, k_plan.hip) and a fixed grid of waves draws tiles from an atomic counter
 // until none are left.
 //
 // Two tile kinds, both running the bitsliced core (bitslice_core.h):
