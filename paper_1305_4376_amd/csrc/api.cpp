@@ -13,7 +13,7 @@ hipError_t launch_auto(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint
     if (n_blocks <= kPairTo) return launch_pair_ecb(ks, in, out, n_blocks, stream);
     if (n_blocks <= kTableTo) return launch_table(ks, in, out, n_blocks, stream);
     if (n_blocks <= kPairAgainTo) return launch_pair_ecb(ks, in, out, n_blocks, stream);
-    if (n_blocks < kTeamBelow) return launch_team_ecb(ks, in, out, n_blocks, stream);
+    if (n_blocks <= kTeamTo) return launch_team_ecb(ks, in, out, n_blocks, stream);
     return launch_bitslice(ks, in, out, n_blocks, stream);
 }
 

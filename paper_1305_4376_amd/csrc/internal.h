@@ -78,15 +78,18 @@ hipError_t launch_pair_cbc_decrypt(const uint32_t *ks, const uint8_t *in, uint8_
 //   to kTableTo         the table kernel: 6.4 us at 65536, 6.6 at 2^17, 9.8 at 2^18, where each lane has one
 //                       block (with a second pass 16.1 from there on);
 //   to kPairAgainTo     two lanes per block: 13.2 us at 5 * 2^16, 14.7 at 3 * 2^17;
-//   below kTeamBelow    a team per tile: 14.8 us from the shortest message to 3 * 2^17, 30.6 at 2^21, 43 at
-//                       3 * 2^20, where one wave per tile takes 39 (35.1 at 2^21);
+//   to kTeamTo          a team per tile: 14.8 us from the shortest message to 3 * 2^17, 30.6 at 2^21 (four
+//                       teams per CU), 36.7 behind it, where one wave per tile takes 34.6 (31.9 at 2^21);
 //   from there on       one wave per tile.
-// The modes have no one-lane table kernel: two lanes per block from kShortBelow to kPairAgainTo.
+// The modes have no one-lane table kernel: two lanes per block from kShortBelow to kPairAgainTo.  Their extra
+// work costs a lone wave more, so teams take them to kModeTeamBelow: CTR 31.2 us at 2^21 (a wave per tile 39.7),
+// CBC decryption 31.1 (37.0).
 constexpr uint64_t kShortBelow = 12288;
 constexpr uint64_t kPairTo = 90112;
 constexpr uint64_t kTableTo = 1ull << 18;
 constexpr uint64_t kPairAgainTo = 3ull << 17;
-constexpr uint64_t kTeamBelow = 9ull << 18;
+constexpr uint64_t kTeamTo = 1ull << 21;
+constexpr uint64_t kModeTeamBelow = 9ull << 18;
 hipError_t launch_auto(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, hipStream_t stream);
 // Block-parallel modes (bitsliced): ks is the encryption half for CTR and the
 // decryption half for CBC decryption; iv is the 8 IV bytes read as a big-endian integer.

@@ -128,7 +128,7 @@ hipError_t launch_ctr(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint6
                       hipStream_t stream) {
     if (n_blocks < kShortBelow) return launch_short_ctr(ks, in, out, n_blocks, iv, stream);
     if (n_blocks <= kPairAgainTo) return launch_pair_ctr(ks, in, out, n_blocks, iv, stream);
-    if (n_blocks < kTeamBelow) return launch_team_ctr(ks, in, out, n_blocks, iv, stream);
+    if (n_blocks < kModeTeamBelow) return launch_team_ctr(ks, in, out, n_blocks, iv, stream);
     return launch<TileMode::kCtr>(ks, in, out, n_blocks, iv, stream);
 }
 
@@ -136,7 +136,7 @@ hipError_t launch_cbc_decrypt(const uint32_t *ks, const uint8_t *in, uint8_t *ou
                               hipStream_t stream) {
     if (n_blocks < kShortBelow) return launch_short_cbc_decrypt(ks, in, out, n_blocks, iv, stream);
     if (n_blocks <= kPairAgainTo) return launch_pair_cbc_decrypt(ks, in, out, n_blocks, iv, stream);
-    if (n_blocks < kTeamBelow) return launch_team_cbc_decrypt(ks, in, out, n_blocks, iv, stream);
+    if (n_blocks < kModeTeamBelow) return launch_team_cbc_decrypt(ks, in, out, n_blocks, iv, stream);
     return launch<TileMode::kCbcDecrypt>(ks, in, out, n_blocks, iv, stream);
 }
 

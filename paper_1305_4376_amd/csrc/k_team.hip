@@ -26,7 +26,7 @@ __global__ __launch_bounds__(kTeamThreads) void tdes_team_kernel(const uint32_t 
 
 template <TileMode kMode>
 hipError_t launch(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks, uint64_t iv, hipStream_t stream) {
-    const uint32_t tiles = (uint32_t)((n_blocks + kTileBlocks - 1) / kTileBlocks);  // n_blocks is below kTeamBelow
+    const uint32_t tiles = (uint32_t)((n_blocks + kTileBlocks - 1) / kTileBlocks);  // n_blocks is below kModeTeamBelow
     hipLaunchKernelGGL(tdes_team_kernel<kMode>, dim3(tiles), dim3(kTeamThreads), 0, stream, ks, in, out, n_blocks, iv);
     return hipGetLastError();
 }

@@ -31,7 +31,7 @@ def _check(guard, dst, offset, want):
     assert bool((guard[offset + dst.numel():] == 0xA5).all()) and bool((guard[:offset] == 0xA5).all())
 
 
-@pytest.mark.parametrize("n", [393215, 393216, 393217, 327679, 327680, 327681, 331000, 2359295, 2359296, 2359297, 2361343])
+@pytest.mark.parametrize("n", [393215, 393216, 393217, 327679, 327680, 327681, 331000, 2097151, 2097152, 2097153, 2099199, 2359295, 2359296, 2359297, 2361343])
 @pytest.mark.parametrize("offset", [0, 8])
 def test_ecb_around_the_team_range(n, offset):
     print(f"[team] ecb n={n} offset={offset}", flush=True)
