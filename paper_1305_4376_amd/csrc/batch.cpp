@@ -37,9 +37,10 @@ namespace {
 constexpr uint32_t kWaveBlocks = 2048;
 constexpr uint32_t kLaneBlocks = 32;
 constexpr uint32_t kLanesPerTile = 64;
-// Default cut-over: a remainder this long still takes a wave tile.  A lane
-// tile costs about 14% more per block (per-lane key masks), so a wave tile
-// wins above ~1800 blocks; the autotuner may choose another value.
+// Default cut-over: a remainder this long still takes a wave tile.  A lane tile
+// costs more per block (a key per lane); the autotuner may choose another value,
+// and for 4096 messages does: 1536, 1.4% faster (360.0 -> 355.1 us).  The default
+// is what the interface states.
 constexpr uint32_t kDefaultWaveRemainder = 1800;
 constexpr uint32_t kMaxTilesPerDraw = 16;
 constexpr uint64_t kMaxJobBlocks = 1ull << 40;
