@@ -1,6 +1,6 @@
 // k_batch_team.hip -- a batch too small to fill the chip with one wave per tile: a workgroup per tile.
 //
-// A wave takes 36 us for a tile however few there are (41 for a lane tile), so a batch of up to
+// A wave takes over 30 us for a tile however few there are (more for a lane tile), so a batch of up to
 // kTeamTiles tiles shares each of them between the eight waves of a workgroup (team_core.h), lane tiles
 // with every lane's own key too.  In a captured graph the grid is the largest, so that one graph serves
 // every such batch; workgroups past the last tile end at once.

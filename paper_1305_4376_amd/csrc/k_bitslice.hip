@@ -11,10 +11,11 @@
 // wave each); its code has only that path, so it fits 128 VGPRs and runs four
 // waves per SIMD.  Tiles beyond 2^22 per launch loop grid-stride.  A partial
 // last tile runs beside the whole ones, one bit of f per lane (short_core.h):
-// a wave alone on it would take 33 us.  Buffers that are only 8-byte aligned
+// a wave alone on it would take 31 us.  Buffers that are only 8-byte aligned
 // take the same path (3000001 blocks behind an 8-byte header: 43.4 us a call
 // with per-block accesses and a wave on the last block, 43.2 with 16-byte
-// accesses and the last block behind the others, 40.2 beside them).  The key
+// accesses and the last block behind the others, 40.2 beside them; with the
+// present circuits and transposes 36.1).  The key
 // is the same for the whole launch, so its masks come from scalar registers.
 #include <hip/hip_runtime.h>
 

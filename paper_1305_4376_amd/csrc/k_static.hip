@@ -46,7 +46,7 @@ constexpr uint32_t kThreads = 256;
 constexpr uint32_t kGroupsPerCU = 4;
 constexpr uint64_t kMaxJobBlocks = 1ull << 40;
 // Teams up to here, waves from there on: 1400 tiles 57.6 us by the small kernel and 58.1 by two, 1700 59.6 and
-// 60.6, 2000 65.4 and 64.8.
+// 60.6, 2000 65.4 and 64.8; with smaller circuits 1100 45.1 and 50.7, 1300 54.8 and 53.5, 1500 55.6 and 55.7.
 constexpr uint32_t kStaticTeamTiles = 1600;
 constexpr uint32_t kSmallJobs = 4096;              // eight per thread of a team
 constexpr uint32_t kLaneBlocks = 32;

@@ -1,8 +1,8 @@
 // team_core.h -- the bitsliced rounds on one tile of 2048 blocks, shared by a team of eight waves.
 //
-// A wave that runs a tile alone (bitslice_core.h) needs all its 13.6 k vector
+// A wave that runs a tile alone (bitslice_core.h) needs all its 11.5 k vector
 // instructions one after the other, and a wave alone on its SIMD issues one
-// only every 4.9 cycles (two waves: every 2.35): 33 us a tile, however empty
+// only every 4.9 cycles (two waves: every 2.35): 31 us a tile, however empty
 // the chip is.  Here a workgroup of eight waves takes the tile.  Wave s
 // computes box s of every round and keeps in registers the four planes of each
 // half that the box's outputs go to; all planes lie in LDS too, from where a
@@ -11,8 +11,8 @@
 // exactly as in bitslice_core.h (bitslice_maps.h), in LDS too; when every lane
 // has its own key, the six inputs are XORed with its key masks instead.
 //
-// Bound: a round of a team alone on its CU is its chain, about 480 cycles: 34
-// vector instructions (170), the reads' and the writes' way through LDS (100
+// Bound: a round of a team alone on its CU is its chain, about 460 cycles: 29
+// vector instructions (145), the reads' and the writes' way through LDS (100
 // each; LDS takes 2.2 cycles for a plane read and 3.1 for one written), the
 // wait for the slowest box at the barrier.  With several teams on a CU it is
 // vector issue and LDS together.
