@@ -238,8 +238,10 @@ int tdes_ctx_destroy(tdes_ctx *ctx);
 
 /*
  * Encrypt or decrypt every message of a batch: ECB on each message as in
- * tdes_ecb_encrypt/decrypt, all messages in one launch of a persistent kernel
- * (captured in a graph, for tdes_ecb_batch_replay, unless TDES_BATCH_NO_GRAPH).
+ * tdes_ecb_encrypt/decrypt, all messages in one launch of a persistent kernel.
+ * Unless TDES_BATCH_NO_GRAPH, a context's first batch also captures the launch in a
+ * graph for tdes_ecb_batch_replay, after it is enqueued (a failed capture fails no
+ * batch); a replay captures whatever graph is still missing.
  *   jobs: host, n_jobs entries; read before the call returns.
  *   dev_sched_table: device, n_scheds schedules written by tdes_sched_upload.
  *   dev_base: device; every offset is relative to it.
@@ -256,7 +258,8 @@ int tdes_ecb_batch(tdes_ctx *ctx, const tdes_job *jobs, uint32_t n_jobs, const v
 
 /*
  * Run the last planned batch again (same messages, keys and buffers) without
- * planning or copying: one graph launch.  flags: 0 or TDES_BATCH_NO_GRAPH.
+ * planning or copying: one graph launch (captured by the call if the context has
+ * none for these buffers and launch shape).  flags: 0 or TDES_BATCH_NO_GRAPH.
  * Errors: TDES_ERR_NULL, TDES_ERR_ARG, TDES_ERR_STATE (no batch yet), TDES_ERR_HIP.
  */
 int tdes_ecb_batch_replay(tdes_ctx *ctx, uint32_t flags, void *stream);
