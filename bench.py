@@ -228,7 +228,7 @@ def bench_serving(td, torch, inputs, dev, batch_capacity_bps, seconds, tuning=No
                                        max_step_blocks=step_blocks, tuning=shape,
                                        backlog_step_blocks=backlog_step_blocks)
         try:
-            # Warm-up: the first 5% of the trace (graph captures, plan buffers, first allocations), not measured.
+            # Warm-up: the first 5% of the trace (plan buffers, first allocations), not measured.
             n_warm = max(200, len(reqs) // 20)
             td.tdes_server_run_trace(server, reqs[:n_warm], arrival[:n_warm] - arrival[0])
             td.tdes_server_wait_idle(server, 60)

@@ -315,8 +315,9 @@ int launch_step(tdes_server *s, Step &st) {
             tdes::launch_fill_tiles(st.d_fill, (uint32_t)st.fills.size(), s->d_pool, st.stream) != hipSuccess)
             return TDES_ERR_HIP;
     }
-    int rc = tdes_ecb_batch(st.ctx, st.jobs.data(), (uint32_t)st.jobs.size(), s->sched, s->n_scheds, s->d_pool, 0,
-                            st.stream);
+    // (no step is replayed: no graph)
+    int rc = tdes_ecb_batch(st.ctx, st.jobs.data(), (uint32_t)st.jobs.size(), s->sched, s->n_scheds, s->d_pool,
+                            TDES_BATCH_NO_GRAPH, st.stream);
     if (rc != TDES_OK) return rc;
     for (size_t i = 0; i < st.ids.size(); i++) {
         const tdes_request &rq = st.rq[i];

@@ -1,4 +1,4 @@
-// The host side of the batch calls (csrc/batch.cpp) over a runtime that does no GPU work: it logs the calls and
+// The host side of the batch calls (csrc/batch.cpp) and of the server (csrc/serve.cpp) over a runtime that does no GPU work: it logs the calls and
 // fails the one it is told to.  argv: a scenario; prints the log, one call a line.
 #include <stdio.h>
 #include <stdlib.h>
@@ -51,6 +51,9 @@ hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
 hipError_t hipMemset(void *p, int v, size_t n) { memset(p, v, n); return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { return make(s); }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipMemcpyAsync(void *to, const void *from, size_t n, hipMemcpyKind, hipStream_t) { memcpy(to, from, n); return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return make(e); }
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
@@ -85,6 +88,7 @@ hipError_t launch_auto(const uint32_t *, const uint8_t *, uint8_t *, uint64_t, h
 hipError_t launch_plan(const PlanMessage *, uint32_t, uint32_t, PlanHeader *, Slot *, uint32_t, uint32_t, hipStream_t s) {
     return launched("plan", s);
 }
+hipError_t launch_fill_tiles(const FillTile *, uint32_t, uint8_t *, hipStream_t s) { return launched("fill", s); }
 hipError_t launch_batch(const uint32_t *, const PlanHeader *, const Slot *, uint32_t *, uint8_t *, uint32_t, uint32_t,
                         uint32_t, bool, hipStream_t s) {
     return launched("waves", s);
@@ -105,6 +109,24 @@ void batch(tdes_ctx *c, uint64_t n_blocks, uint8_t *base, uint32_t flags = 0) {
     printf("batch %d\n", tdes_ecb_batch(c, &job, 1, g_table, 1, base, flags, nullptr));
 }
 
+// A server with one step in flight: two requests of n blocks, one after the other.
+int serve(uint64_t n) {
+    tdes_serve_config cfg{};
+    cfg.budget_bytes = 16 * n + 4096;
+    cfg.max_inflight = 1;
+    cfg.max_step_jobs = 8;
+    cfg.max_step_blocks = n;
+    tdes_server *s = nullptr;
+    if (tdes_server_create(&s, &cfg, g_table, 1) != TDES_OK) return 2;
+    for (int i = 0; i < 2; i++) {
+        tdes_request r{};
+        r.n_blocks = n;
+        const int rc = tdes_server_submit(s, &r, nullptr), idle = tdes_server_wait_idle(s, 30);
+        printf("served %d %d\n", rc, idle);
+    }
+    return tdes_server_destroy(s);
+}
+
 void replay(tdes_ctx *c) { printf("replay %d\n", tdes_ecb_batch_replay(c, 0, nullptr)); }
 
 }  // namespace
@@ -113,6 +135,7 @@ int main(int argc, char **argv) {
     setvbuf(stdout, nullptr, _IOLBF, 0);
     const std::string what = argc > 1 ? argv[1] : "";
     const uint64_t n = argc > 2 ? strtoull(argv[2], nullptr, 10) : 100;
+    if (what == "serve") return serve(n);
     tdes_ctx *c = nullptr;
     if (tdes_ctx_create(&c, 0) != TDES_OK) return 2;
     if (what == "ordinary") {
