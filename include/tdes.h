@@ -203,7 +203,11 @@ typedef struct tdes_job {
  * launch shape.  Not thread-safe: one host thread at a time per context. */
 typedef struct tdes_ctx tdes_ctx;
 
-/* Statistics of the last planned batch and the context's launch shape. */
+/* A batch of at most this many tiles has a workgroup for each of them, without a work counter; more are drawn by
+ * the persistent kernel's waves.  Only that kernel has the launch shape and the tiles per draw of tdes_ctx_set_tuning. */
+#define TDES_BATCH_TEAM_TILES 2048
+
+/* Statistics of the last planned batch and the context's settings. */
 typedef struct tdes_batch_info {
     uint64_t tiles;          /* work items of the last batch */
     uint64_t wave_tiles;     /* ... of up to 2048 blocks of one message */
@@ -211,7 +215,7 @@ typedef struct tdes_batch_info {
     uint64_t slots;          /* slot descriptors of the plan */
     uint64_t blocks;         /* message blocks in the batch */
     uint64_t padded_blocks;  /* block positions computed (tiles x 2048) */
-    uint32_t threads;        /* threads per workgroup of the batch kernel */
+    uint32_t threads;        /* threads per workgroup of the persistent kernel */
     uint32_t groups_per_cu;  /* workgroups per compute unit in its grid */
     uint32_t graph_captures; /* graphs captured so far by this context */
     uint32_t wave_remainder; /* a message's last partial tile of at least this many blocks is a wave tile */
@@ -249,7 +253,8 @@ int tdes_ctx_destroy(tdes_ctx *ctx);
  * and that no message writes bytes another message reads or writes (only
  * exact in-place is allowed).  The plan is written on the device by a kernel
  * on `stream`; the call can block until the previous batch's has run.  A batch
- * of few tiles shares each of them between the waves of a workgroup.
+ * of at most TDES_BATCH_TEAM_TILES tiles shares each of them between the waves of
+ * a workgroup.
  * Errors: TDES_ERR_NULL, TDES_ERR_ARG, TDES_ERR_ALIGN, TDES_ERR_SIZE,
  * TDES_ERR_OVERLAP, TDES_ERR_NOMEM, TDES_ERR_HIP.
  */
@@ -275,7 +280,9 @@ int tdes_ecb_batch_replay(tdes_ctx *ctx, uint32_t flags, void *stream);
  *                   key per lane); 1..2048, 0 for the default (1800);
  *   tiles_per_draw: tiles a wave takes per draw from the work counter after
  *                   its first; 1..16, 0 for the default (1).
- * Applies to the next batch (a new plan and graph capture when it changes).
+ * Applies to the next batch (a new plan and graph capture when it changes).  threads,
+ * groups_per_cu and tiles_per_draw are the persistent kernel's: a batch of at most
+ * TDES_BATCH_TEAM_TILES tiles runs without them.
  * Errors: TDES_ERR_NULL, TDES_ERR_ARG.
  */
 int tdes_ctx_set_tuning(tdes_ctx *ctx, uint32_t threads, uint32_t groups_per_cu, uint32_t wave_remainder,
@@ -359,7 +366,8 @@ typedef struct tdes_serve_config {
     uint64_t max_step_blocks; /* blocks per step (a request larger than this runs alone) */
     uint32_t keep_outputs;    /* nonzero: outputs stay in device memory until tdes_server_release */
     uint32_t pad;
-    /* Tuning of every step's batch (tdes_ctx_set_tuning); threads == 0 keeps the library's defaults for all four. */
+    /* Tuning of every step's batch (tdes_ctx_set_tuning, with the same limit for steps of few tiles);
+       threads == 0 keeps the library's defaults for all four. */
     uint32_t threads, groups_per_cu, wave_remainder, tiles_per_draw;
     /* Backlog-sized steps: while the queue holds more than max_inflight * max_step_blocks blocks, a
        step may take up to (queued blocks / max_inflight) blocks, at most this many.  0, or a value

@@ -19,7 +19,7 @@ __all__ = [
     "TDES_VARIANT_AUTO", "TDES_VARIANT_TABLE", "TDES_VARIANT_BITSLICE", "TDES_SCHED_BYTES",
     "tdes_expand_key", "tdes_sched_upload", "tdes_ecb_encrypt", "tdes_ecb_decrypt", "tdes_ecb_run",
     "tdes_status_str", "tdes_fill_splitmix64", "library_path", "load_library",
-    "JOB_DTYPE", "TDES_BATCH_NO_GRAPH", "TDES_BATCH_PER_MESSAGE", "tdes_ctx_create", "tdes_ctx_destroy",
+    "JOB_DTYPE", "TDES_BATCH_NO_GRAPH", "TDES_BATCH_PER_MESSAGE", "TDES_BATCH_TEAM_TILES", "tdes_ctx_create", "tdes_ctx_destroy",
     "tdes_ecb_batch", "tdes_ecb_batch_replay", "tdes_ctx_set_tuning", "tdes_ctx_get_info",
     "REQUEST_DTYPE", "COMPLETION_DTYPE", "tdes_server_create", "tdes_server_destroy", "tdes_server_now",
     "tdes_server_submit", "tdes_server_cancel", "tdes_server_poll", "tdes_server_wait_idle",
@@ -35,6 +35,7 @@ TDES_CHECK_PARITY, TDES_REJECT_WEAK = 1, 2
 TDES_VARIANT_AUTO, TDES_VARIANT_TABLE, TDES_VARIANT_BITSLICE = 0, 1, 2
 TDES_SCHED_BYTES = 1600
 TDES_BATCH_NO_GRAPH, TDES_BATCH_PER_MESSAGE = 1, 2
+TDES_BATCH_TEAM_TILES = 2048
 TDES_STATIC_MAX_JOBS = 65536
 
 # struct tdes_job (include/tdes.h): 32 bytes.

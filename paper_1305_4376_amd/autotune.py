@@ -6,7 +6,9 @@ persistent, and four parameters shape a launch: threads per workgroup (waves
 per workgroup), workgroups per compute unit, the wave/lane cut-over (a
 message's last partial tile of at least this many blocks runs as a wave tile
 with one key per wave, a shorter one as 32-block lane slots with one key per
-lane) and tiles per draw from the work counter.  `tune_batch` times graph
+lane) and tiles per draw from the work counter.  A batch of at most
+TDES_BATCH_TEAM_TILES tiles runs on a kernel without a launch shape or a work
+counter, so only the cut-over is a choice there.  `tune_batch` times graph
 replays of a real batch through the C ABI: every launch shape first, then the
 tiling axes at the best shape; it applies the fastest to the context and
 records it in a JSON cache keyed by (GPU architecture, compute units, kernel,
@@ -69,6 +71,11 @@ def apply_cached(ctx: int, blocks: int, kernel: str = "batch", path: str = CACHE
     return tuning
 
 
+def _shaped(ctx: int) -> bool:
+    """Whether the launch shape and the tiles per draw matter to the context's last batch."""
+    return td.tdes_ctx_get_info(ctx)["tiles"] > td.TDES_BATCH_TEAM_TILES
+
+
 def _time_replays(ctx: int, tuning, reps: int) -> float:
     import torch
     td.tdes_ctx_set_tuning(ctx, *tuning)
@@ -87,23 +94,29 @@ def tune_batch(ctx: int, jobs, dev_sched_table, n_scheds: int, dev_base, reps: i
 
     Launch shapes first (threads x workgroups per CU, default tiling), then the tiling axes at
     the best shape.  A change of the wave/lane cut-over re-plans the batch, so those candidates
-    run tdes_ecb_batch once before their replays."""
+    run tdes_ecb_batch once before their replays.  Axes that a batch of few tiles has no use for
+    are not timed, and stay as the context has them (the shape) or at their default (one tile a draw)."""
     import torch
     default_tiling = (0, 0)
+    info = td.tdes_ctx_get_info(ctx)
+    shape = (info["threads"], info["groups_per_cu"])
     td.tdes_ecb_batch(ctx, jobs, dev_sched_table, n_scheds, dev_base, 0)
     torch.cuda.synchronize()
     timings = []
-    for threads in THREADS:
-        for gpc in GROUPS_PER_CU:
-            tuning = (threads, gpc) + default_tiling
-            timings.append((_time_replays(ctx, tuning, reps), tuning))
-    best = min(timings)[1]
+    if _shaped(ctx):
+        for threads in THREADS:
+            for gpc in GROUPS_PER_CU:
+                tuning = (threads, gpc) + default_tiling
+                timings.append((_time_replays(ctx, tuning, reps), tuning))
+        shape = min(timings)[1][:2]
     for rem in WAVE_REMAINDER:
         for per_draw in TILES_PER_DRAW:
-            tuning = best[:2] + (rem, per_draw)
+            tuning = shape + (rem, per_draw)
             td.tdes_ctx_set_tuning(ctx, *tuning)
             td.tdes_ecb_batch(ctx, jobs, dev_sched_table, n_scheds, dev_base, 0)  # plan with this cut-over
             timings.append((_time_replays(ctx, tuning, reps), tuning))
+            if not _shaped(ctx):
+                break
     timings.sort()
     best_t, tuning = timings[0]
     td.tdes_ctx_set_tuning(ctx, *tuning)

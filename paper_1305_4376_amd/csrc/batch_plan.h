@@ -3,6 +3,8 @@
 #include <stdint.h>
 #include <hip/hip_runtime.h>
 
+#include "../../include/tdes.h"
+
 namespace tdes {
 
 // Plan buffer on the device: [PlanHeader][slots].  Slots: 64 per lane tile, then one per wave tile.
@@ -61,7 +63,7 @@ hipError_t launch_batch_capped(const uint32_t *sched, const PlanHeader *hdr, con
 // teams / by waves: 1152 whole tiles 41 / -, 1400 46 / 53, 2000 58 / 60, 2300 65 / 63; with lane tiles among
 // them 234 (18 of them) 22.5 / 46, 1466 (239) 48 / 55, 1949 (313) 60 / 60.  Whole calls with the present,
 // smaller circuits: 1100 whole tiles 43.7 / 52.3, 1500 49.7 / 56.9, 1900 60.9 / 61.6.
-constexpr uint32_t kTeamTiles = 2048;
+constexpr uint32_t kTeamTiles = TDES_BATCH_TEAM_TILES;
 hipError_t launch_batch_team(const uint32_t *sched, const PlanHeader *hdr, const Slot *slots, uint8_t *base,
                              uint32_t grid, hipStream_t stream);  // grid: at least the tiles
 
