@@ -46,8 +46,6 @@ constexpr uint32_t kDefaultWaveRemainder = 1800;
 constexpr uint32_t kMaxTilesPerDraw = 16;
 constexpr uint64_t kMaxJobBlocks = 1ull << 40;
 
-size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
-
 }  // namespace
 
 struct tdes_ctx {

@@ -352,17 +352,19 @@ __device__ __forceinline__ uint32_t tile_count(uint64_t left) {
 // A wave tile: 2048 consecutive blocks starting at `tin`/`tout` (wave-uniform),
 // blocks first_block.. of the message; lane l holds blocks 128k + 2l and
 // 128k + 2l + 1 (k = 0..15), so each access is 16 bytes per lane over 1 KiB
-// contiguous across the wave.  kFull: all 2048 blocks valid.  Otherwise each
+// contiguous across the wave.  kFull: all 2048 blocks valid.  Otherwise (ECB only:
+// a mode's partial tile is enciphered one bit of f per lane, short_core.h) each
 // block is loaded and stored on its own, at the same addresses, only if it is
 // one of the first n_valid; lanes past the end compute on zeros.  Buffers are
-// 8-byte aligned; the hardware takes 16-byte accesses at any 4-byte address.  Whole-tile loads and stores are nontemporal (every block
-// is read and written once), except CBC decryption's first read, which is read
-// again after the rounds.
+// 8-byte aligned; the hardware takes 16-byte accesses at any 4-byte address.
+// Whole-tile loads and stores are nontemporal (every block is read and written
+// once), except CBC decryption's first read, which is read again after the rounds.
 typedef unsigned int v4u __attribute__((ext_vector_type(4), aligned(8)));
 
 template <TileMode kMode, bool kFull>
 __device__ __forceinline__ void mode_tile(const uint32_t *__restrict__ ks, const uint8_t *tin, uint8_t *tout,
                                           uint32_t n_valid, uint32_t lane, uint64_t first_block, uint64_t iv) {
+    static_assert(kFull || kMode == TileMode::kEcb, "no mode has partial wave tiles");
     uint32_t a[32], b[32];
     lane = opaque(lane);
     if constexpr (kMode == TileMode::kCtr) {
@@ -398,7 +400,7 @@ __device__ __forceinline__ void mode_tile(const uint32_t *__restrict__ ks, const
     // lane 0 the last block of the previous 128 (carried in scalars; for k = 0 the block before the
     // tile, or the IV at the message's start).
     uint32_t carry_a = be_hi_word(iv), carry_b = be_lo_word(iv);
-    if (kMode == TileMode::kCbcDecrypt && kFull && first_block != 0) {
+    if (kMode == TileMode::kCbcDecrypt && first_block != 0) {
         const uint2 v = *reinterpret_cast<const uint2 *>(tin - 8);
         carry_a = __builtin_amdgcn_readfirstlane(v.x);
         carry_b = __builtin_amdgcn_readfirstlane(v.y);
@@ -408,30 +410,16 @@ __device__ __forceinline__ void mode_tile(const uint32_t *__restrict__ ks, const
         const uint32_t j = 128 * k + 2 * lane;
         const uint8_t *p = tin + 1024 * k + 16 * lane;
         if constexpr (kMode == TileMode::kCtr) {  // the keystream meets the data
-            if (kFull) {
-                const v4u v = __builtin_nontemporal_load(reinterpret_cast<const v4u *>(p));
-                a[2 * k] ^= v.x; b[2 * k] ^= v.y; a[2 * k + 1] ^= v.z; b[2 * k + 1] ^= v.w;
-            } else {
-                uint2 v0 = make_uint2(0, 0), v1 = make_uint2(0, 0);
-                if (j < n_valid) v0 = *reinterpret_cast<const uint2 *>(p);
-                if (j + 1 < n_valid) v1 = *reinterpret_cast<const uint2 *>(p + 8);
-                a[2 * k] ^= v0.x; b[2 * k] ^= v0.y; a[2 * k + 1] ^= v1.x; b[2 * k + 1] ^= v1.y;
-            }
+            const v4u v = __builtin_nontemporal_load(reinterpret_cast<const v4u *>(p));
+            a[2 * k] ^= v.x; b[2 * k] ^= v.y; a[2 * k + 1] ^= v.z; b[2 * k + 1] ^= v.w;
         } else if constexpr (kMode == TileMode::kCbcDecrypt) {  // XOR the preceding ciphertext blocks
-            if (kFull) {
-                const v4u v = __builtin_nontemporal_load(reinterpret_cast<const v4u *>(p));  // blocks j, j + 1
-                constexpr int kWaveShr1 = 0x138;  // DPP: lane i reads lane i - 1; lane 0 keeps the old value
-                const uint32_t pa = (uint32_t)__builtin_amdgcn_update_dpp((int)carry_a, (int)v.z, kWaveShr1, 0xF, 0xF, false);
-                const uint32_t pb = (uint32_t)__builtin_amdgcn_update_dpp((int)carry_b, (int)v.w, kWaveShr1, 0xF, 0xF, false);
-                a[2 * k] ^= pa; b[2 * k] ^= pb; a[2 * k + 1] ^= v.x; b[2 * k + 1] ^= v.y;
-                carry_a = __builtin_amdgcn_readlane(v.z, kLanes - 1);
-                carry_b = __builtin_amdgcn_readlane(v.w, kLanes - 1);
-            } else {
-                uint2 v0 = make_uint2(be_hi_word(iv), be_lo_word(iv)), v1 = make_uint2(0, 0);
-                if (first_block + j != 0 && j < n_valid) v0 = *reinterpret_cast<const uint2 *>(p - 8);
-                if (j + 1 < n_valid) v1 = *reinterpret_cast<const uint2 *>(p);
-                a[2 * k] ^= v0.x; b[2 * k] ^= v0.y; a[2 * k + 1] ^= v1.x; b[2 * k + 1] ^= v1.y;
-            }
+            const v4u v = __builtin_nontemporal_load(reinterpret_cast<const v4u *>(p));  // blocks j, j + 1
+            constexpr int kWaveShr1 = 0x138;  // DPP: lane i reads lane i - 1; lane 0 keeps the old value
+            const uint32_t pa = (uint32_t)__builtin_amdgcn_update_dpp((int)carry_a, (int)v.z, kWaveShr1, 0xF, 0xF, false);
+            const uint32_t pb = (uint32_t)__builtin_amdgcn_update_dpp((int)carry_b, (int)v.w, kWaveShr1, 0xF, 0xF, false);
+            a[2 * k] ^= pa; b[2 * k] ^= pb; a[2 * k + 1] ^= v.x; b[2 * k + 1] ^= v.y;
+            carry_a = __builtin_amdgcn_readlane(v.z, kLanes - 1);
+            carry_b = __builtin_amdgcn_readlane(v.w, kLanes - 1);
         }
         uint8_t *q = tout + 1024 * k + 16 * lane;
         if (kFull) {
