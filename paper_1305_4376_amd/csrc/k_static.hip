@@ -51,6 +51,10 @@ constexpr uint32_t kStaticTeamTiles = 1600;
 constexpr uint32_t kSmallJobs = 4096;              // eight per thread of a team
 constexpr uint32_t kLaneBlocks = 32;
 constexpr uint32_t kWaveRemainder = 1800;          // a remainder of at least this many blocks is a wave tile
+// Buffers for which the small kernel is launched alone are smaller than this (most_tiles below): 23 MB.  An accepted
+// job has at most that many bytes, so kSmallJobs of them have fewer than 2^32 tiles or slots, whatever they share.
+constexpr uint64_t kAloneBytes = 8ull * kWaveRemainder * kStaticTeamTiles;
+static_assert(kSmallJobs * (kAloneBytes / (8 * kTileBlocks) + kTileBlocks / kLaneBlocks) < 1ull << 32, "sums of tiles");
 
 // scratch: [header, 256 B][tile_start: kMaxJobs + 1 words]
 struct StaticHeader {
@@ -208,8 +212,7 @@ __device__ __forceinline__ JobTiles job_tiles(const tdes_job &x, bool ok) {
 }
 
 // The whole call by teams if its tiles are few, else its plan.  n_jobs <= kSmallJobs.  alone: no cipher kernel
-// follows; scratch is not touched, and every tile is the teams' (base_bytes is then below 2^24, and the sums
-// fit 32 bits).
+// follows; scratch is not touched, and every tile is the teams' (the sums fit 32 bits: kAloneBytes below).
 __global__ __launch_bounds__(kTeamThreads) void tdes_static_small_kernel(const tdes_job *__restrict__ jobs, uint32_t n_jobs,
                                                                          const uint32_t *__restrict__ sched,
                                                                          uint64_t n_scheds, uint8_t *scr, uint8_t *base,
