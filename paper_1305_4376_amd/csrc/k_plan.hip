@@ -23,9 +23,13 @@ constexpr uint32_t kWaveBlocks = 2048, kLaneBlocks = 32;
 constexpr uint32_t kMaxGridX = 1u << 13, kMaxGridY = 64;
 constexpr uint32_t kTilesPerGroup = 256;  // wave slots of a message that one wave writes, up to kMaxGridY workgroups
 
-__global__ __launch_bounds__(kThreads) void tdes_plan_kernel(const tdes::PlanMessage *messages, uint32_t n_messages,
-                                                             tdes::PlanHeader *hdr, tdes::Slot *slots, uint32_t n_tiles,
-                                                             uint32_t n_lane_slots) {
+// Held to 32 VGPRs (the attribute counts pairs; it takes 30 without a spill, and 34 if left alone): what four waves of
+// the server's cipher kernel leave on a SIMD.  With 34 the plan of a step waited until workgroups of the step
+// before retired: 156 us a plan instead of 35 (8 on an empty GPU), and the saturated server delivered 982 GB/s
+// instead of 1013.
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(16))) void tdes_plan_kernel(
+    const tdes::PlanMessage *messages, uint32_t n_messages, tdes::PlanHeader *hdr, tdes::Slot *slots, uint32_t n_tiles,
+    uint32_t n_lane_slots) {
     __shared__ alignas(8) uint32_t records[kGroupMessages * kRecordWords];
     const uint32_t n_lane_tiles = (n_lane_slots + kLanes - 1) / kLanes;
     const uint32_t lane = threadIdx.x % kLanes, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
