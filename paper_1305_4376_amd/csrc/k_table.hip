@@ -41,9 +41,21 @@ namespace {
 using namespace tdes_table;
 
 // Threads per workgroup: more waves share a workgroup's tables and hide the round's chain, fewer start
-// sooner.  256 / 512 / 1024 threads: 2^14 blocks 6.1 / 6.3 / 9.1 us, 2^16 6.4 / 6.5 / 9.2, 2^17 7.2 / 6.7 /
-// 9.3, 2^18 11.1 / 9.9 / 9.5, 2^19 19.0 / 16.6 / 16.1, 3 * 2^18 27.3 / 21.9 / 26.7.
-constexpr uint32_t default_threads(uint64_t n_blocks) { return n_blocks <= 1u << 16 ? 256 : 512; }
+// sooner.  256 / 512 / 1024 threads: 2^14 blocks 6.1 / 6.3 / 9.1 us, 2^16 6.6 / 6.7 / 9.3, 2^17 7.2 / 6.7 /
+// 9.3, 2^18 10.9 / 9.9 / 9.6, 2^19 19.1 / 16.6 / 16.2, 3 * 2^18 27.4 / 22.0 / 26.8, 2^20 35.4 / 30.4 / 27.2.
+// A launch works in passes of two blocks per resident lane, and one that needs the lanes of only one workgroup
+// per CU is short.  Behind an odd number of its passes such a short one costs 256 threads less than what is left
+// of the pass of 512: 300000 blocks 15.7 us against 16.2, 400000 18.6 against 16.4; 860000 29.0 against 30.1,
+// 1000000 35.3 against 30.4; from 2^20 on 512 are ahead throughout (1400000 45.0 against 43.8).  (A first
+// workgroup of 512 that is not full ends early: 2^18 + 2 blocks 14.7 against 11.9.  An odd last block, which the
+// grid's first lane takes alone, costs 256 threads more: 263169 blocks 18.4 against 16.3.)
+// resident: workgroups on the chip, two per CU.
+uint32_t default_threads(uint64_t n_blocks, uint64_t resident) {
+    if (n_blocks <= 256 * (resident / 2)) return 256;
+    const uint64_t pass = 2 * 256 * resident;  // blocks of a pass of 256 threads: 2^18
+    const uint64_t passes = (n_blocks - 1) / pass, over = n_blocks - passes * pass;
+    return (passes == 1 || passes == 3) && over > 2 * 512 && over <= pass / 2 && n_blocks % 2 == 0 ? 256 : 512;
+}
 
 __constant__ SpTables g_sp = make_sp();
 
@@ -191,9 +203,9 @@ hipError_t launch_table(const uint32_t *ks, const uint8_t *in, uint8_t *out, uin
                         hipStream_t stream, uint32_t threads) {
     DeviceInfo info;
     if (device_info(&info) != TDES_OK) return hipErrorInvalidDevice;
-    if (threads == 0) threads = default_threads(n_blocks);
     // 64 KiB of LDS per workgroup: two per CU (the compiler fits the registers of every size to that)
     const uint64_t resident = (uint64_t)info.cu_count * 2;
+    if (threads == 0) threads = default_threads(n_blocks, resident);
     // One block per lane while one pass of the resident grid covers the message, else two.
     const int per_lane = n_blocks <= resident * threads ? 1 : 2;
     const uint64_t units = n_blocks / per_lane;
