@@ -1,8 +1,8 @@
 """GPU parity of the allocation-free batch on each of its routes, with jobs it must refuse first, in the middle
 and last, and with a plan of an earlier, larger call left in its scratch array.
 
-Routes: one launch; one launch that finds few tiles in a large buffer; at most 4096 jobs with more tiles than
-teams take (the first launch leaves a plan for the second); more than 4096 jobs (a plan kernel).  Every byte of the
+Routes: one launch (also with 512 jobs, from where on its threads take several, and with more than the 2048 that are
+read at a time); one launch that finds few tiles in a large buffer; at most 4096 jobs with more tiles than teams take (the first launch leaves a plan for the second); more than 4096 jobs (a plan kernel).  Every byte of the
 buffer is compared with plain launches of the accepted messages, and the count of the refused ones.  Tolerance:
 0 bits.
 """
@@ -19,6 +19,9 @@ N_KEYS = 9
 SEED = 0xC32
 ROUTES = {
     "one launch": ([3000, 100, 2048, 77, 5000, 64, 1] * 4, 0),
+    "512 jobs, one for each thread": ([1 + j % 70 for j in range(512)], 0),
+    "513 jobs": ([1 + j % 70 for j in range(513)], 0),
+    "2049 jobs, more than are read at a time": ([1 + j % 40 for j in range(2049)], 0),
     "few tiles in a large buffer": ([3000, 100, 2048, 77, 5000, 64, 1] * 4, 48 << 20),
     "two launches, one plans": ([2049 + 5 * j for j in range(1000)], 0),
     "a plan kernel": ([1 + j % 90 for j in range(4200)], 0),
