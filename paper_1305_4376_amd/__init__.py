@@ -166,7 +166,7 @@ def _stream(stream, like=None):
         return stream if isinstance(stream, int) else stream.cuda_stream
     import torch
     dev = like.device if hasattr(like, "device") and like.device.type == "cuda" else None
-    return torch.cuda.current_stream(dev).cuda_stream
+    return _torch()[1](torch.cuda.current_device() if dev is None else dev.index)
 
 
 def _nbytes(x) -> int | None:
@@ -208,15 +208,18 @@ def _nblocks(buf, n_blocks):
 def _message_args(dev_sched, src, dst, n_blocks, stream=None):
     """(schedule, input, output, block count, stream) of a one-message call as the C entry takes them,
     with every sized buffer checked against the call."""
-    if n_blocks is None and stream is None:
-        # The ordinary call, tensors without a count or a stream.  Its host time is most of a short
-        # message's, so each fact is asked of torch once, and anything unusual goes the general way.
+    if n_blocks is None or type(n_blocks) is int:
+        # The ordinary call, on tensors.  Its host time is most of a short message's, so each fact is asked of
+        # torch once, and anything unusual goes the general way.
         tensor, raw_stream = _torch()
         if type(src) is tensor and type(dst) is tensor and type(dev_sched) is tensor:
             index, have = src.get_device(), src.nbytes
-            if (index >= 0 and not have % 8 and dst.nbytes >= have and dev_sched.nbytes >= TDES_SCHED_BYTES
+            need = have if n_blocks is None else 8 * n_blocks
+            if (index >= 0 and not need % 8 and 0 <= need <= have and dst.nbytes >= need
+                    and dev_sched.nbytes >= TDES_SCHED_BYTES
                     and src.is_contiguous() and dst.is_contiguous() and dev_sched.is_contiguous()):
-                return dev_sched.data_ptr(), src.data_ptr(), dst.data_ptr(), have // 8, raw_stream(index)
+                return dev_sched.data_ptr(), src.data_ptr(), dst.data_ptr(), need // 8, (
+                    raw_stream(index) if stream is None else _stream(stream))
     n = _nblocks(src, n_blocks)
     _need(dev_sched, TDES_SCHED_BYTES, "schedule")
     _need(src, 8 * n, "input")
