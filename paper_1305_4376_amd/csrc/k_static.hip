@@ -212,7 +212,14 @@ __device__ __forceinline__ JobTiles job_tiles(const tdes_job &x, bool ok) {
 }
 
 // The whole call by teams if its tiles are few, else its plan.  n_jobs <= kSmallJobs.  alone: no cipher kernel
-// follows; scratch is not touched, and every tile is the teams' (the sums fit 32 bits: kAloneBytes below).
+// follows; scratch is not touched, and every tile is the teams' (the sums fit 32 bits: kAloneBytes).
+//
+// kMany: more jobs than threads.  The jobs are read by neighbouring lanes, four of a thread's in flight, and their counts
+// go by way of the planes' LDS to the threads that sum consecutive jobs.  (Read by each thread for its own eight, 256
+// bytes apart between lanes, and again for the plan: 4000 whole tiles 95.6 us instead of 88.4, 4096 jobs of up to 4096
+// blocks, by the teams, 59.6 instead of 50.7.)  With a job per thread there is nothing to gain, and a kernel with both
+// ways in it took 512 records 22.35 us instead of 22.14.
+template <bool kMany>
 __global__ __launch_bounds__(kTeamThreads) void tdes_static_small_kernel(const tdes_job *__restrict__ jobs, uint32_t n_jobs,
                                                                          const uint32_t *__restrict__ sched,
                                                                          uint64_t n_scheds, uint8_t *scr, uint8_t *base,
@@ -224,43 +231,46 @@ __global__ __launch_bounds__(kTeamThreads) void tdes_static_small_kernel(const t
     __shared__ uint32_t part_lane[8], part_ragged[8], part_bad[8];
     const uint32_t tid = threadIdx.x, lane = tid % kLanes, wv = tid / kLanes;
     const uint32_t per = (n_jobs + kTeamThreads - 1) / kTeamThreads;
-    // Every job's wave tiles and lane slots, a refused one's marked, by way of the planes' LDS: read by neighbouring
-    // lanes, four jobs of a thread in flight, while a thread then sums consecutive jobs.  (Read by each thread for its own
-    // eight, 256 bytes apart between lanes, and again for the plan: 4000 whole tiles 95.6 us instead of 88.4, 4096
-    // jobs of up to 4096 blocks, by the teams, 59.6 instead of 50.7.)
+    uint32_t *job_wave = lds, *job_slots = lds + kSmallJobs;  // (kMany) each job's wave tiles; lane slots or kRefused
     constexpr uint32_t kRefused = 1u << 31;
     static_assert(2 * kSmallJobs <= kTeamLaneWords && kTileBlocks / kLaneBlocks < kRefused, "room for the counts");
-    uint32_t *job_wave = lds, *job_slots = lds + kSmallJobs;
-    auto count = [&](uint32_t j, const tdes_job &x) {
-        const bool ok = job_ok(x, n_scheds, base_bytes);
-        const JobTiles t = job_tiles(x, ok);
-        job_wave[j] = t.wave;
-        job_slots[j] = ok ? t.slots : kRefused;
-    };
-    if (per == 1) {  // each thread reads its own job, and its own counts
-        if (tid < n_jobs) count(tid, jobs[tid]);
-    } else {
+    // the thread's jobs: wave tiles, lane slots, jobs with lane slots, refused jobs
+    uint64_t wave = 0;
+    uint32_t slots = 0, ragged = 0, bad = 0;
+    if constexpr (kMany) {
         constexpr uint32_t kAhead = 4;  // jobs in flight
         for (uint32_t j = tid; j < n_jobs; j += kAhead * kTeamThreads) {
             tdes_job x[kAhead];
 #pragma unroll
             for (uint32_t i = 0; i < kAhead; i++) x[i] = jobs[min(j + i * kTeamThreads, n_jobs - 1)];
 #pragma unroll
-            for (uint32_t i = 0; i < kAhead; i++)
-                if (j + i * kTeamThreads < n_jobs) count(j + i * kTeamThreads, x[i]);
+            for (uint32_t i = 0; i < kAhead; i++) {
+                const uint32_t at = j + i * kTeamThreads;
+                if (at >= n_jobs) break;
+                const bool ok = job_ok(x[i], n_scheds, base_bytes);
+                const JobTiles t = job_tiles(x[i], ok);
+                job_wave[at] = t.wave;
+                job_slots[at] = ok ? t.slots : kRefused;
+            }
         }
         __syncthreads();
-    }
-    // the thread's jobs: wave tiles, lane slots, jobs with lane slots, refused jobs
-    const uint32_t my_first = tid * per, my_end = min(n_jobs, my_first + per);
-    uint64_t wave = 0;
-    uint32_t slots = 0, ragged = 0, bad = 0;
-    for (uint32_t j = my_first; j < my_end; j++) {
-        const uint32_t n = job_slots[j] & ~kRefused;
-        wave += job_wave[j];
-        slots += n;
-        ragged += n != 0;
-        bad += job_slots[j] >> 31;
+        for (uint32_t j = tid * per; j < min(n_jobs, (tid + 1) * per); j++) {
+            const uint32_t n = job_slots[j] & ~kRefused;
+            wave += job_wave[j];
+            slots += n;
+            ragged += n != 0;
+            bad += job_slots[j] / kRefused;
+        }
+    } else {
+        for (uint32_t j = tid * per; j < min(n_jobs, (tid + 1) * per); j++) {
+            const tdes_job x = jobs[j];
+            const bool ok = job_ok(x, n_scheds, base_bytes);
+            const JobTiles t = job_tiles(x, ok);
+            wave += t.wave;
+            slots += t.slots;
+            ragged += t.slots != 0;
+            bad += !ok;
+        }
     }
     // inclusive sums over the wave's threads, then over the waves
     uint64_t w = wave;
@@ -300,9 +310,14 @@ __global__ __launch_bounds__(kTeamThreads) void tdes_static_small_kernel(const t
         }
         if (!mine && !overflow) {
             uint32_t run = (uint32_t)(w - wave) + (g - ragged);
-            for (uint32_t j = my_first; j < my_end; j++) {
+            for (uint32_t j = tid * per; j < min(n_jobs, (tid + 1) * per); j++) {
                 tile_start[j] = run;
-                run += job_wave[j] + ((job_slots[j] & ~kRefused) != 0);
+                if constexpr (kMany) {
+                    run += job_wave[j] + ((job_slots[j] & ~kRefused) != 0);
+                } else {
+                    const tdes_job x = jobs[j];
+                    if (job_ok(x, n_scheds, base_bytes)) run += (uint32_t)((x.n_blocks + kTileBlocks - 1) / kTileBlocks);
+                }
             }
             if (tid == 0) tile_start[n_jobs] = (uint32_t)by_job;
         }
@@ -413,9 +428,9 @@ extern "C" int tdes_ecb_batch_static(const tdes_job *dev_jobs, uint32_t n_jobs, 
         const uint64_t most_tiles = base_bytes / (8 * kWaveRemainder) + n_jobs / kLanes + 2;
         const bool alone = most_tiles <= kStaticTeamTiles;
         const uint32_t resident = (uint32_t)info.cu_count * 3;  // 45 KiB of LDS per workgroup
-        hipLaunchKernelGGL(tdes_static_small_kernel, dim3(most_tiles < resident ? (uint32_t)most_tiles : resident),
-                           dim3(kTeamThreads), 0, s, dev_jobs, n_jobs, table, n_scheds, scr, base, base_bytes, dev_rejected,
-                           alone);
+        hipLaunchKernelGGL(n_jobs > kTeamThreads ? tdes_static_small_kernel<true> : tdes_static_small_kernel<false>,
+                           dim3(most_tiles < resident ? (uint32_t)most_tiles : resident), dim3(kTeamThreads), 0, s,
+                           dev_jobs, n_jobs, table, n_scheds, scr, base, base_bytes, dev_rejected, alone);
         if (hipGetLastError() != hipSuccess) return TDES_ERR_HIP;
         if (alone) return TDES_OK;
     } else {
