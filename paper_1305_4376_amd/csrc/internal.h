@@ -48,7 +48,7 @@ class DeviceGuard {
 
 // Kernel launchers.  Arguments are already validated; n_blocks > 0.
 // `ks` points at the words of one direction.  threads: workgroup size, 0 for
-// the kernel's own (256; the table kernel's is 512 above 2^16 blocks); otherwise
+// the kernel's own (256; the table kernel's mostly 512 above 2^16 blocks); otherwise
 // 64, 128, 256, 512 or 1024 (hipErrorInvalidValue for anything else).
 hipError_t launch_table(const uint32_t *ks, const uint8_t *in, uint8_t *out, uint64_t n_blocks,
                         hipStream_t stream, uint32_t threads = 0);
@@ -78,8 +78,8 @@ hipError_t launch_pair_cbc_decrypt(const uint32_t *ks, const uint8_t *in, uint8_
 //   to kTableTo         the table kernel: 6.4 us at 65536, 6.6 at 2^17, 9.8 at 2^18, where each lane has one
 //                       block (with a second pass 16.1 from there on);
 //   to kPairAgainTo     two lanes per block: 13.2 us at 5 * 2^16, 14.7 at 3 * 2^17;
-//   to kTeamTo          a team per tile: 14.8 us from the shortest message to 3 * 2^17, 30.6 at 2^21 (four
-//                       teams per CU), 36.7 behind it, where one wave per tile takes 34.6 (31.9 at 2^21);
+//   to kTeamTo          a team per tile: 14.6 us at 3 * 2^17, 14.9 at 2^19, 29.4 at 2^21 (one wave per tile
+//                       31.6), 36.7 behind it, where one wave per tile takes 34.6;
 //   from there on       one wave per tile.
 // The modes have no one-lane table kernel: two lanes per block from kShortBelow to kPairAgainTo.  Their extra
 // work costs a lone wave more, so teams take them to kModeTeamBelow: CTR 31.2 us at 2^21 (a wave per tile 39.7),

@@ -71,7 +71,7 @@ __global__ __launch_bounds__(kDefaultThreads, kWavesPerSimd) void tdes_bitslice_
     }
 }
 
-// ECB of a message shorter than a tile, by one wave: what TDES_VARIANT_BITSLICE asks for by name (36 us, where
+// ECB of a message shorter than a tile, by one wave: what TDES_VARIANT_BITSLICE asks for by name (31 us, where
 // the automatic choice takes 3).
 __global__ __launch_bounds__(kLanes) void tdes_bitslice_tail_kernel(const uint32_t *__restrict__ ks, const uint8_t *in,
                                                                     uint8_t *out, uint32_t n_blocks) {

@@ -4,8 +4,8 @@
 // one wave per tile (k_bitslice.hip), each tile of 2048 blocks is shared by the eight waves of a workgroup
 // (team_core.h).  A partial last tile runs beside the others in the same launch.
 //
-// Measured back to back (us a launch, team / table / one wave per tile): 2^18 blocks 14.9 / 9.9 / 31,
-// 2^19 14.8 / 16.6 / 31, 2^20 20.1 / 35 / 31.5, 3 * 2^19 26.0 / - / 32.0, 2^21 30.6 / 66 / 31.9.  One tile
+// Measured back to back (us a launch, team / table / one wave per tile): 3 * 2^17 blocks 14.6 / 16.3 / 30.0,
+// 2^19 14.9 / 16.5 / 30.5, 2^20 18.7 / 30.4 / 30.7, 3 * 2^19 23.9 / 44.0 / 31.0, 2^21 29.4 / 57.3 / 31.6.  One tile
 // per CU is 2^19 blocks; a launch without rounds (loads, transposes, stores) takes 3.6 us.
 #include <hip/hip_runtime.h>
 
