@@ -90,17 +90,6 @@ __device__ __forceinline__ void transpose32(uint32_t (&w)[32]) {
     for (int i = 0; i < 32; i++) w[i] = __builtin_rotateright32(t[i], i);
 }
 
-// The same by exchange stages, for the way into the rounds with a key per lane: the compiler then assigns those
-// rounds other registers, and 8125 lane tiles take 231 us instead of 252, 300000 messages of up to 64 blocks 166
-// instead of 185.  (On the way out it makes no difference.)
-__device__ __forceinline__ void transpose32_exchange(uint32_t (&w)[32]) {
-    exchange_stage<16, 0x0000FFFFu>(w);
-    exchange_stage<8, 0x00FF00FFu>(w);
-    exchange_stage<4, 0x0F0F0F0Fu>(w);
-    exchange_stage<2, 0x33333333u>(w);
-    exchange_stage<1, 0x55555555u>(w);
-}
-
 // ---- rounds ----
 
 __device__ __forceinline__ uint32_t key_mask(uint32_t word, int pos) {
@@ -283,13 +272,8 @@ __device__ __forceinline__ void des_stage_folded(uint32_t (&x)[32], uint32_t (&y
 // words, one key XOR per S-box input).
 template <bool kLaneKeys>
 __device__ __forceinline__ void tdes_32_blocks(uint32_t (&a)[32], uint32_t (&b)[32], const uint32_t *__restrict__ ks) {
-    if constexpr (kLaneKeys) {
-        transpose32_exchange(a);
-        transpose32_exchange(b);
-    } else {
-        transpose32(a);
-        transpose32(b);
-    }
+    transpose32(a);
+    transpose32(b);
     uint32_t l[32], r[32];
 #pragma unroll
     for (int k = 0; k < 32; k++) {
@@ -344,13 +328,13 @@ __device__ __forceinline__ uint32_t opaque(uint32_t v) {
     return v;
 }
 
-// For words that a branch has loaded: makes them opaque behind it.  Otherwise the compiler moves the transposes'
-// first rotations into the branch, to each load, and waits for every load before it issues the next (60 of the
-// batch kernel's 84): 4063 lane tiles took 167 us instead of 137, the static batch of 2000 messages of 1801 blocks
-// 76 instead of 71.
-__device__ __forceinline__ void loaded(uint32_t (&a)[32], uint32_t (&b)[32]) {
+// For words first .. first + n - 1 (constants), loaded behind a condition: makes them opaque there.  Otherwise the
+// compiler moves the transposes' first rotations to the loads, and waits for every load before it issues the next (60
+// of the batch kernel's 84): 4063 lane tiles took 167 us instead of 137, the static batch of 2000 messages of 1801
+// blocks 76 instead of 71.
+__device__ __forceinline__ void loaded(uint32_t (&a)[32], uint32_t (&b)[32], int first, int n) {
 #pragma unroll
-    for (int j = 0; j < 32; j++) {
+    for (int j = first; j < first + n; j++) {
         a[j] = opaque(a[j]);
         b[j] = opaque(b[j]);
     }
@@ -420,7 +404,7 @@ __device__ __forceinline__ void mode_tile(const uint32_t *__restrict__ ks, const
                 a[2 * k] = v0.x; b[2 * k] = v0.y; a[2 * k + 1] = v1.x; b[2 * k + 1] = v1.y;
             }
         }
-        if constexpr (!kFull) loaded(a, b);
+        if constexpr (!kFull) loaded(a, b, 0, 32);
     }
     tdes_32_blocks<false>(a, b, ks);
     lane = opaque(lane);
@@ -469,7 +453,9 @@ __device__ __forceinline__ void wave_tile(const uint32_t *__restrict__ ks, const
 }
 
 // A lane slot: up to 32 consecutive blocks owned by this lane alone (its own
-// message, key and direction).  count = 0 leaves the lane idle.
+// message, key and direction).  count = 0 leaves the lane idle.  Eight loads at a time: every lane's go to lines of
+// its own, and with one in flight, or all 32 of every wave, it is slower (8125 lane tiles 235 us, with 32 in flight
+// 252, with one 289; 300000 messages of up to 64 blocks 167, 185, 183).
 __device__ __forceinline__ void lane_slot(const uint32_t *ks, const uint8_t *lin, uint8_t *lout, uint32_t count) {
     uint32_t a[32], b[32];
     if (count) {
@@ -478,12 +464,13 @@ __device__ __forceinline__ void lane_slot(const uint32_t *ks, const uint8_t *lin
             const uint32_t jj = opaque(j < (int)count ? j : count - 1);
             const uint2 v = *reinterpret_cast<const uint2 *>(lin + 8 * jj);
             a[j] = v.x; b[j] = v.y;
+            if (j % 8 == 7) loaded(a, b, j - 7, 8);
         }
     } else {
 #pragma unroll
         for (int j = 0; j < 32; j++) a[j] = b[j] = 0;
     }
-    loaded(a, b);
+    loaded(a, b, 0, 32);
     tdes_32_blocks<true>(a, b, ks);
     if (count) {
 #pragma unroll

@@ -25,7 +25,7 @@ constexpr uint32_t kTilesPerGroup = 256;  // wave slots of a message that one wa
 
 // Held to 32 VGPRs (the attribute counts pairs; it takes 30 without a spill, and 34 if left alone): what four waves of
 // the server's cipher kernel leave on a SIMD.  With 34 the plan of a step waited until workgroups of the step
-// before retired: 156 us a plan instead of 35 to 49 (8 on an empty GPU), and the saturated server delivered 982 GB/s
+// before retired: 156 us a plan instead of 35 to 50 (8 on an empty GPU), and the saturated server delivered 982 GB/s
 // instead of 1013.
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(16))) void tdes_plan_kernel(
     const tdes::PlanMessage *messages, uint32_t n_messages, tdes::PlanHeader *hdr, tdes::Slot *slots, uint32_t n_tiles,

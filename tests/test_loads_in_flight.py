@@ -1,5 +1,5 @@
 """The loads of a tile are in flight together, also where each of them hangs on a condition (partial wave tiles and
-lane tiles): read from the assembly that the kernels are compiled to (no GPU needed).  A wave that waits for each of
+lane tiles, eight at a time): read from the assembly that the kernels are compiled to (no GPU needed).  A wave that waits for each of
 its 32 loads before it issues the next has 32 trips to memory one after the other.
 """
 import os
@@ -35,4 +35,4 @@ def test_tile_loads_do_not_wait_for_each_other(source, kernel, tile_loads, tmp_p
                            os.path.join(build.CSRC, source)], stderr=subprocess.DEVNULL)
     loads, waited = _waited_at_once(out.read_text(), kernel)
     assert loads >= tile_loads
-    assert waited < 10, f"{waited} of {loads}"  # counters, slots, key words and the last load of each kind of tile
+    assert 4 * waited <= loads, f"{waited} of {loads}"  # counters, slots, key words, and the last of every group of loads
